@@ -342,12 +342,15 @@ gmc_status gmc_set_step(gmc_ctx* ctx, int64_t t);
  * Tuning and test options (value semantics per option):
  *   GMC_OPT_FORCE_FULL_SELECT  1: every top-s selection takes the full-data
  *                              path (no speculative candidates)
- *   GMC_OPT_CAND_MARGIN        rank of the next step's speculative threshold,
- *                              in quarters of k (4..4096; default 4: the
- *                              threshold sits at the floor of the 22-bit key
- *                              bin holding this step's key of rank k, and
- *                              the residual's growth brings about 1.3-2 k
- *                              candidates the next step)
+ *   GMC_OPT_CAND_MARGIN        least rank of the next step's speculative
+ *                              threshold, in quarters of k (4..4096; default
+ *                              4).  Exact top-s sets the threshold at the
+ *                              floor of the 22-bit key bin holding this
+ *                              step's key of that rank, or of a larger one
+ *                              (at most about 2 k + 8 sqrt(k)) when the
+ *                              residual no longer grows from step to step,
+ *                              so that about 1.04 k candidates or more are
+ *                              there the next step
  *   GMC_OPT_CAND_CAP_MULT      candidate capacity as a multiple of k (>= 1);
  *                              reallocates scratch; before the first step
  *   GMC_OPT_PROFILE            bit mask of the stages to time with HIP events

@@ -98,7 +98,7 @@ struct WorkerPtrs {
 // Per (worker, segment) pair state, kept in device memory across kernels.
 struct PairState {
     uint32_t tau;       // candidate threshold key of the next fused pass
-    uint32_t unused0;
+    uint32_t tau_rank;  // keys at or above tau when it was set (0: not known)
     int32_t mode;       // 0 = resolve from candidates, 1 = full data, 3 = full data collected
                         // by the second pass (kModeCollected)
     uint32_t prefix;    // radix digits fixed so far
@@ -108,7 +108,8 @@ struct PairState {
     uint32_t done;      // finished workgroups of the current kernel
     uint32_t cand_used; // candidates of this step (cand is reset for the next)
     uint32_t tau_used;  // the candidate threshold this step's fused pass used
-    uint32_t unused1, unused2;
+    float growth;       // smoothed cand_used / tau_rank of the steps so far (0: not known)
+    uint32_t unused;
     // exact top-s: the first pass puts the next step's threshold at the floor
     // of the 11-bit bin tau_bin holding the key of rank margin*k/4; with
     // tau_fine the second pass narrows it to the floor of the 22-bit bin

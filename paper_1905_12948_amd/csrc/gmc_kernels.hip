@@ -1009,9 +1009,39 @@ hipError_t launch_topk_seed(const StepArgs& a, const TopkGeometry& g, const Topk
     return hipGetLastError();
 }
 
-// margin: the speculative threshold's rank, in quarters of k.  h2/gh2: the
-// second pass's histogram of the threshold's bin (PASS 2 only; gh2 holds it
-// unless that bin is the one h covers).
+// The rank at which the next step's speculative threshold is set.  Of the
+// keys at or above a threshold, `growth` times as many reach it one step
+// later: 1.2-2 while the residual builds up, but 1.0 once it has (after about
+// n/k steps a component is sent as often as it reaches the threshold), and
+// then rank k leaves too few candidates every other step, which costs a
+// full-data selection (d = 2^20, K = 4, 1%: 188 us per step after 2000 steps
+// against 69 us; d = 11.2M, K = 8, 1%: 360 against 282 us).
+// So the rank aims at k + k/32 + 4 sqrt(k) candidates (the fluctuation of a
+// count, and 3% for steps that differ), but is never below margin * k / 4.
+// growth: smoothed over the steps, quick to fall and slow to rise, 0.8 until
+// it is known.
+constexpr uint32_t kTauStep = 1u << 17;  // a 64th of an octave of keys
+
+__device__ __forceinline__ uint64_t next_rank(int kp, int cap, int margin, uint32_t cand, uint32_t tau_prev,
+                                              uint32_t rank_prev, float* growth) {
+    float gr = *growth;
+    if (tau_prev != kNoThreshold && rank_prev != 0u) {
+        const float now = fminf(fmaxf((float)cand / (float)rank_prev, 0.5f), 2.0f);
+        gr = (gr == 0.0f || now < gr) ? now : gr + 0.03125f * (now - gr);
+    }
+    *growth = gr;
+    const float k = (float)kp;
+    const float target = (k + 0.03125f * k + 4.0f * sqrtf(k)) / (gr == 0.0f ? 0.8f : gr);
+    const uint64_t least = ((uint64_t)margin * (uint64_t)kp + 3) / 4;
+    // no further than halfway from k to the capacity
+    const uint64_t most = (uint64_t)kp + (uint64_t)(cap - kp) / 2;
+    const uint64_t aim = (uint64_t)target < most ? (uint64_t)target : most;
+    return aim > least ? aim : least;
+}
+
+// margin: the least rank of the speculative threshold, in quarters of k.
+// h2/gh2: the second pass's histogram of the threshold's bin (PASS 2 only;
+// gh2 holds it unless that bin is the one h covers).
 template <int PASS>
 __device__ void finish_digit(PairState* ps, int p, uint32_t* h, uint32_t* gh, int kp, int mode, uint32_t cand,
                              uint32_t prefix, int margin, int force_full, bool approx, const TopkGeometry& g,
@@ -1027,6 +1057,9 @@ __device__ void finish_digit(PairState* ps, int p, uint32_t* h, uint32_t* gh, in
     // counts in issue order)
     const uint32_t need = PASS == 1 ? (uint32_t)kp : (uint32_t)ps->need;
     const uint32_t tau_prev = PASS == 1 ? ps->tau : 0u;
+    const uint32_t rank_prev = PASS == 1 ? ps->tau_rank : 0u;
+    const float growth_prev = PASS == 1 ? ps->growth : 0.0f;
+    const uint32_t T_prev = PASS == 1 ? ps->T : 0u;
     const uint32_t tau_fine = PASS == 2 ? ps->tau_fine : 0u;
     const uint32_t tau_bin = PASS == 2 ? ps->tau_bin : 0u;
     const uint32_t tau_need = PASS == 2 ? ps->tau_need : 0u;
@@ -1046,14 +1079,16 @@ __device__ void finish_digit(PairState* ps, int p, uint32_t* h, uint32_t* gh, in
 
     if (PASS == 1) {
         // speculative threshold of the next step: the floor of the bin that
-        // holds the key of rank margin*k/4 this step (the second pass of
-        // exact top-s narrows it to 22 bits)
-        const uint64_t want64 = ((uint64_t)margin * (uint64_t)kp + 3) / 4;
+        // holds the key of rank `want` this step (the second pass of exact
+        // top-s narrows it to 22 bits)
+        float growth = growth_prev;
+        const uint64_t want64 = approx ? ((uint64_t)margin * (uint64_t)kp + 3) / 4
+                                       : next_rank(kp, g.pair_cap[p], margin, cand, tau_prev, rank_prev, &growth);
         uint32_t total, want, ab2 = 0;
         int tb;
         if (want64 == (uint64_t)need && bin >= 0) {
-            // rank k itself (the default margin): T's bin, found above, in a
-            // histogram of at least k keys
+            // rank k itself (a growing residual, the default margin): T's
+            // bin, found above, in a histogram of at least k keys
             total = want = need;
             ab2 = above;
             tb = bin;
@@ -1066,10 +1101,29 @@ __device__ void finish_digit(PairState* ps, int p, uint32_t* h, uint32_t* gh, in
         }
         if (threadIdx.x == 0) {
             const bool widen = want64 > total;
-            if (widen && tb > 0) --tb;  // too few counted: widen by one bin
             if (tb < 0) tb = 0;
+            uint32_t tau = (uint32_t)tb << kShift1;
+            if (widen) {
+                // too few counted (they all reach tau_prev): below that
+                // threshold by as much as its last distance from T held per
+                // key (ps->T and rank_prev are still the previous step's), or
+                // the next bin where there was no threshold or the whole
+                // sample is counted
+                if (!approx && mode == 0) {
+                    uint32_t step = kTauStep;
+                    if (rank_prev > (uint32_t)kp && T_prev > tau_prev) {
+                        const float per_key = (float)(T_prev - tau_prev) / (float)(rank_prev - (uint32_t)kp);
+                        step = (uint32_t)fminf(per_key * (float)(want64 - total) + 512.0f, (float)kTauStep);
+                    }
+                    tau = tau_prev > step ? tau_prev - step : 0u;
+                } else if (tb > 0) {
+                    tau = (uint32_t)(tb - 1) << kShift1;
+                }
+            }
             ps->tau_used = tau_prev;
-            ps->tau = (uint32_t)tb << kShift1;
+            ps->tau = tau;
+            ps->tau_rank = (uint32_t)(want64 < 0xffffffffull ? want64 : 0xffffffffull);
+            ps->growth = growth;
             ps->tau_fine = (!approx && !widen) ? 1u : 0u;
             ps->tau_bin = (uint32_t)tb;
             ps->tau_need = want - ab2;
