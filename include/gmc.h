@@ -130,8 +130,8 @@ gmc_status gmc_set_segments(gmc_ctx* ctx, int32_t n_seg, const int64_t* seg_off)
 
 /* GMC_RBGS only: block length B of the random blockwise compressor (RBGS,
  * Sections 4 and 5.2: whole blocks of consecutive components, drawn with a
- * seed the workers share).  1 <= B <= d; a multiple of 4 takes the vector
- * path, any B is accepted.  Before the first step only (GMC_ESTATE after).
+ * seed the workers share).  1 <= B <= d; any B is accepted, a multiple of 4
+ * is faster (a 16-byte access then never straddles blocks).  Before the first step only (GMC_ESTATE after).
  * Default 4096. */
 gmc_status gmc_set_block(gmc_ctx* ctx, int32_t block);
 
@@ -182,7 +182,8 @@ int64_t gmc_count(int64_t n, double ratio);
  *                         top-s: the number kept)
  * Device buffers must not overlap each other, except that w_t_dev and
  * w_prev_dev may be one buffer (w_{-1} = w_0 at t = 0).  Pointers that are not
- * 16-byte aligned are accepted (slower path).  w is never written.
+ * 16-byte aligned are accepted (a wavefront's accesses then touch one cache
+ * line more).  w is never written.
  */
 gmc_status gmc_step(gmc_ctx* ctx, const float* w_t_dev, const float* w_prev_dev,
                     const float* const* grads_dev, float* const* err_dev,
@@ -446,8 +447,8 @@ gmc_status gmc_pair_stats(gmc_ctx* ctx, int32_t* mode, int64_t* cand, int32_t n,
 /*
  * Stage timings of the stages GMC_OPT_PROFILE selects: for each stage i < n,
  * total milliseconds and timed launches since the option was last set.
- * Stages: 0 fused worker pass (vector kernel; RBGS: its fused gather pass),
- * 1 fused worker pass (element-wise kernel), 2 selection (RBGS: block draw),
+ * Stages: 0 fused worker pass (RBGS: its fused gather pass), 1 not used (no
+ * launches), 2 selection (RBGS: block draw),
  * 3 emit, 4 aggregate, 5 apply.  Synchronises the context's stream.
  */
 gmc_status gmc_profile_read(gmc_ctx* ctx, double* ms, int64_t* launches, int32_t n);

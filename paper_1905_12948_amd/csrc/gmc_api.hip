@@ -17,8 +17,7 @@ using namespace gmc;
 
 namespace {
 
-// profiled stages: fused pass (vector kernel), fused pass (element-wise
-// kernel), selection, emit, aggregate, apply
+// profiled stages: fused pass, (not used), selection, emit, aggregate, apply
 constexpr int kStages = 6;
 constexpr int64_t kMaxPendingEvents = 4096;
 
@@ -779,39 +778,15 @@ gmc_status step_impl(gmc_ctx* ctx, const float* w_t_dev, const float* w_prev_dev
                                            ctx->rbgs_rbits, ctx->rbgs_meta, ctx->stream));
         GMC_TRY(prof_end(ctx, 2, ev));
         GMC_TRY(prof_begin(ctx, 0, &ev));
-        uint64_t vec_mask = 0;
-        const bool shared_ok = ((uintptr_t)w_t_dev & 15u) == 0 && ((uintptr_t)w_prev_dev & 15u) == 0 &&
-                               ((uintptr_t)val_dev & 15u) == 0 && (row_v & 3) == 0 && (ctx->block & 3) == 0;
-        for (int k = 0; k < ctx->K && shared_ok; ++k)
-            if ((((uintptr_t)grads_dev[k] | (uintptr_t)err_dev[k] | (uintptr_t)a.wp.y[k]) & 15u) == 0)
-                vec_mask |= 1ull << k;
-        GMC_LAUNCH(ctx, launch_rbgs_fused(a, ctx->K, ctx->block, ctx->rbgs_slot, val_dev, row_v, vec_mask,
-                                          ctx->stream));
+        GMC_LAUNCH(ctx, launch_rbgs_fused(a, ctx->K, ctx->block, ctx->rbgs_slot, val_dev, row_v, ctx->stream));
         GMC_TRY(prof_end(ctx, 0, ev));
     } else {
-        // worker k takes the vector pass when its rows and w_t, w_prev are 16-byte aligned
-        uint64_t vec_mask = 0;
-        const bool w_ok = ((uintptr_t)w_t_dev & 15u) == 0 && ((uintptr_t)w_prev_dev & 15u) == 0;
-        for (int k = 0; k < ctx->K && w_ok; ++k)
-            if ((((uintptr_t)grads_dev[k] | (uintptr_t)err_dev[k] | (uintptr_t)a.wp.y[k]) & 15u) == 0)
-                vec_mask |= 1ull << k;
-        // the vector kernel takes every chunk of the workers in vec_mask
-        // (partial and unaligned ones element-wise); the element-wise kernel
-        // every chunk of the others
-        const uint64_t all = ctx->K == 64 ? ~0ull : ((1ull << ctx->K) - 1ull);
         // the context's first step: speculative thresholds from a sample of u
         if (!ctx->seeded && !ctx->force_full) GMC_LAUNCH(ctx, launch_topk_seed(a, ctx->geo, ctx->scr, ctx->stream));
         ctx->seeded = true;
-        if (vec_mask) {
-            GMC_TRY(prof_begin(ctx, 0, &ev));
-            GMC_LAUNCH(ctx, launch_topk_fused_vec(a, ctx->geo, ctx->scr, vec_mask, ctx->stream));
-            GMC_TRY(prof_end(ctx, 0, ev));
-        }
-        if (vec_mask != all) {
-            GMC_TRY(prof_begin(ctx, 1, &ev));
-            GMC_LAUNCH(ctx, launch_topk_fused_gen(a, ctx->geo, ctx->scr, vec_mask, ctx->stream));
-            GMC_TRY(prof_end(ctx, 1, ev));
-        }
+        GMC_TRY(prof_begin(ctx, 0, &ev));
+        GMC_LAUNCH(ctx, launch_topk_fused_vec(a, ctx->geo, ctx->scr, ctx->stream));
+        GMC_TRY(prof_end(ctx, 0, ev));
         GMC_TRY(prof_begin(ctx, 2, &ev));
         GMC_LAUNCH(ctx, launch_topk_compact(a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, ctx->stream));
         for (int pass = 2; pass <= 3; ++pass)

@@ -9,9 +9,8 @@ namespace gmc {
 
 constexpr int kMaxWorkers = 64;
 
-// Fused worker pass: chunks of kChunk consecutive elements of a segment; the
-// vector kernel gives one workgroup (256 threads x 8 floats) to each (chunk,
-// worker), the element-wise kernel one wavefront.
+// Fused worker pass: chunks of kChunk consecutive elements of a segment, one
+// workgroup (256 threads x 8 floats) per (chunk, worker).
 constexpr int kWave = 64;
 constexpr int kWavesPerGroup = 4;
 constexpr int kGroup = kWave * kWavesPerGroup;  // 256 threads
@@ -283,16 +282,10 @@ struct DetachArgs {
 // ----------------------------------------------------------------------------
 // launchers (gmc_kernels.hip); each returns the launch status
 // ----------------------------------------------------------------------------
-// vec_mask: bit k set when worker k's rows (and w_t, w_prev) are 16-byte
-// aligned.  The vector kernel takes every chunk of those workers, the
-// element-wise kernel every chunk of the others.
 // the first step's speculative thresholds from a sample of u (before the
 // fused pass; pairs whose segment is not sampled keep no threshold)
 hipError_t launch_topk_seed(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, hipStream_t st);
-hipError_t launch_topk_fused_vec(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
-                                 uint64_t vec_mask, hipStream_t st);
-hipError_t launch_topk_fused_gen(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
-                                 uint64_t vec_mask, hipStream_t st);
+hipError_t launch_topk_fused_vec(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, hipStream_t st);
 // count, then copy and the first histogram pass (the copy itself takes it
 // for the pairs of exact top-s that resolve from their candidates)
 hipError_t launch_topk_compact(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full,
@@ -316,10 +309,8 @@ hipError_t launch_rbgs_sample(uint64_t seed, uint64_t t, int32_t nb, int32_t n_s
                               int32_t* block_slot, int32_t* idx, int64_t idx_row,
                               int64_t* msg_len, int32_t* prev, int32_t* visit, uint32_t* rbits, int32_t* meta,
                               hipStream_t st);
-// vec_mask: workers whose rows (g, e, detached points) are 16-byte aligned,
-// with w_t, w_prev and the message rows aligned and B a multiple of 4 (else 0)
 hipError_t launch_rbgs_fused(const StepArgs& a, int32_t K, int32_t B, const int32_t* block_slot,
-                             float* val, int64_t val_row, uint64_t vec_mask, hipStream_t st);
+                             float* val, int64_t val_row, hipStream_t st);
 
 hipError_t launch_agg_rowptr(int32_t K, int32_t d, const int32_t* idx, int64_t idx_row,
                              const int64_t* msg_len, int32_t* rowptr, int32_t n_ranges,

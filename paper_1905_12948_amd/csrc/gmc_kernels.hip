@@ -52,8 +52,27 @@ __device__ __forceinline__ uint32_t wave_prefix_small(uint32_t v, uint32_t* tota
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 
+// The same at any 4-byte alignment: rows of a [K, d] tensor with d not a
+// multiple of 4, and segments that start off 16 bytes.  gfx950 takes 16-byte
+// global accesses at 4-byte alignment; a wavefront's then touch one cache
+// line more.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ld4u(const float* p) {
+    const f4u v = *reinterpret_cast<const f4u*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st4u(float* p, float4 v) {
+    f4u x;
+    x.x = v.x;
+    x.y = v.y;
+    x.z = v.z;
+    x.w = v.w;
+    *reinterpret_cast<f4u*>(p) = x;
+}
+
 // Streaming (nontemporal) access for data touched once per step: the K
-// workers' g and e rows are gigabytes, far beyond any cache level.
+// workers' g and e rows are gigabytes, far beyond any cache level.  Any 4-byte
+// alignment (the four loads become one 16-byte load).
 __device__ __forceinline__ float4 ld4_stream(const float* p) {
     float4 v;
     v.x = __builtin_nontemporal_load(p + 0);
@@ -204,36 +223,47 @@ __host__ __device__ inline int64_t run_order_grid(int64_t n_chunks, int K, int r
     return (n_chunks + run - 1) / run * run * K;
 }
 
-// The previous server pass's mark word of the components at j (a.wbits set).
-// The top-s vector pass loads it before its stream of e and g: a wait for the
-// word then leaves those loads in flight (vmcnt counts in issue order).
-__device__ __forceinline__ uint32_t mark_word(const StepArgs& a, int64_t j) {
-    return a.wbits ? a.wbits[j >> 5] : 0u;
+// The previous server pass's mark words of the four components at j (a.wbits
+// set); split: j may not be a multiple of 4, so the four bits may lie in two
+// words.  The top-s vector pass loads them before its stream of e and g and
+// takes the bits (marks4) after it: a wait for a word then leaves the
+// stream's loads in flight (vmcnt counts in issue order).
+__device__ __forceinline__ uint2 mark_words(const StepArgs& a, int64_t j, bool split) {
+    uint2 w = make_uint2(0u, 0u);
+    if (a.wbits) {
+        w.x = a.wbits[j >> 5];
+        if (split) w.y = a.wbits[(j + 3) >> 5];
+    }
+    return w;
 }
 
-// w_t and w_prev of the four components at j for the worker passes (word:
-// mark_word(a, j)).  With the previous server pass's bitmap (a.wbits),
+__device__ __forceinline__ uint32_t marks4(uint2 w, int64_t j) {
+    const uint32_t o = (uint32_t)j & 31u;
+    return ((o > 28u ? w.y << (32u - o) : 0u) | (w.x >> o)) & 0xfu;
+}
+
+// w_t and w_prev of the four components at j for the worker passes (marked:
+// marks4 of them).  With the previous server pass's bitmap (a.wbits),
 // unmarked components have w_t == w_prev, finite: w_t - w_prev is exactly +0
 // there, so the loads are skipped (w_t is still read when the detached points
 // need it) and the momentum term comes out +0, bit for bit what the dense
 // loads give.
 template <bool kDetach>
-__device__ __forceinline__ void load_w4(const StepArgs& a, int64_t j, uint32_t word, float4* wt, float4* wv) {
+__device__ __forceinline__ void load_w4(const StepArgs& a, int64_t j, uint32_t marked, float4* wt, float4* wv) {
     if (a.wbits) {
-        const uint32_t marked = (word >> (j & 31)) & 0xfu;
         if (marked) {
-            *wt = ld4(a.w_t + j);
-            *wv = ld4(a.w_prev + j);
+            *wt = ld4u(a.w_t + j);
+            *wv = ld4u(a.w_prev + j);
         } else if (kDetach) {
-            *wt = ld4(a.w_t + j);
+            *wt = ld4u(a.w_t + j);
             *wv = *wt;
         } else {
             *wt = *wv = make_float4(0.f, 0.f, 0.f, 0.f);
         }
         return;
     }
-    *wt = ld4(a.w_t + j);
-    *wv = ld4(a.w_prev + j);
+    *wt = ld4u(a.w_t + j);
+    *wv = ld4u(a.w_prev + j);
 }
 
 // GMC+'s detached point from w and the residual: w - q e (Algorithm 2).
@@ -309,9 +339,6 @@ __device__ __forceinline__ void store_agent(uint32_t* p, uint32_t v) {
 // streaming pass takes no atomics; the compaction kernel packs the slots.
 // ---------------------------------------------------------------------------
 
-__device__ void fused_chunk_wave(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int chunk,
-                                 int k, const float* dl);
-
 // w_t - w_prev of the components [start, start + len) (len <= kChunk) from
 // the last server pass's change list into dl (LDS): fl(w_{t+1} - w_t) of
 // every component that pass changed, +0 for the others.  False when a range
@@ -341,9 +368,57 @@ __device__ bool scatter_changes(const StepArgs& a, int start, int len, float* dl
     return ok;
 }
 
+// A segment's partial last chunk (len < kChunk): u of the thread's eight
+// components (the full chunk's, those below len), written over e with the
+// detached points and the sample; returns their candidate flags.  Every load
+// is unconditional (a component past the end reads the chunk's last one), so
+// a thread's loads are all in flight together.  dl (nullable, LDS): w_t -
+// w_prev of the chunk's components (scatter_changes), used instead of the two
+// parameter vectors.
 template <int kRule, bool kDetach, bool kApprox>
-__global__ __launch_bounds__(kGroup) void topk_fused_vec_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
-                                                                uint64_t vec_mask) {
+__device__ uint32_t partial_chunk(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int start, int len,
+                                  int k, uint32_t tau, const float* dl, float4* u) {
+    float* e = a.wp.e[k] + start;
+    const float* gr = a.wp.g[k] + start;
+    constexpr bool kNeedW = kRule != kRuleServerMomentum || kDetach;
+    float ev[8], gv[8], wt[8], wv[8];
+    int o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        o[i] = (int)threadIdx.x * 4 + (i >> 2) * (kGroup * 4) + (i & 3);
+        const int oc = o[i] < len ? o[i] : len - 1;
+        ev[i] = e[oc];
+        gv[i] = gr[oc];
+        wt[i] = wv[i] = 0.0f;
+        if (kNeedW && !dl) {
+            wt[i] = a.w_t[start + oc];
+            wv[i] = a.w_prev[start + oc];
+        }
+    }
+    uint32_t flags = 0;
+    float x[8];
+    const uint64_t sst = kApprox ? sample_state(a.seed, a.t, k) : 0ull;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        x[i] = dl ? rule_u_diff<kRule>(ev[i], gv[i], dl[o[i]], a.c, a.h)
+                  : rule_u<kRule>(ev[i], gv[i], wt[i], wv[i], a.c, a.h);
+        if (o[i] < len) {
+            e[o[i]] = x[i];
+            if (kDetach) a.wp.y[k][start + o[i]] = detached(wt[i], x[i], a.q);
+            flags |= (key_of(x[i]) >= tau ? 1u : 0u) << i;
+            if (kApprox) {
+                const int j = start + o[i], q = j / g.stratum;
+                if (sample_pos(sst, q, g.stratum, a.d) == j) s.samp[(size_t)k * g.samp_n + q] = x[i];
+            }
+        }
+    }
+    u[0] = make_float4(x[0], x[1], x[2], x[3]);
+    u[1] = make_float4(x[4], x[5], x[6], x[7]);
+    return flags;
+}
+
+template <int kRule, bool kDetach, bool kApprox>
+__global__ __launch_bounds__(kGroup) void topk_fused_vec_kernel(StepArgs a, TopkGeometry g, TopkScratch s) {
     __shared__ uint32_t wtot[2][kWavesPerGroup];
     __shared__ union {
         int2 stage[kChunk];  // the chunk's candidates, in index order
@@ -353,124 +428,129 @@ __global__ __launch_bounds__(kGroup) void topk_fused_vec_kernel(StepArgs a, Topk
     int2* const stage = sm.stage;
     int chunk, k;
     run_order(blockIdx.x, g.K, a.run, &chunk, &k);
-    if (chunk >= g.n_chunks || !((vec_mask >> k) & 1ull)) return;  // padding, or the element-wise kernel's
+    if (chunk >= g.n_chunks) return;  // padding of the run order
     // one segment (global top-s): the chunk's place is arithmetic, no table lookup
     const bool one = g.n_seg == 1;
     const int start = one ? chunk * kChunk : g.chunk_start[chunk];
     const int len = one ? min(kChunk, a.d - start) : g.chunk_len[chunk];
-    if ((start & 3) != 0 || len != kChunk) {  // partial or unaligned chunk: element-wise, one wavefront
-        // with w_prev NULL (the last server pass updated w in place) w_t -
-        // w_prev exists only in that pass's change list, which holds whole
-        // ranges
-        const float* dl = nullptr;
-        if (a.w_prev == nullptr) {
-            scatter_changes(a, start, len, sm.dl, dl_cnt);
-            dl = sm.dl;
-        }
-        if (threadIdx.x < kWave) fused_chunk_wave(a, g, s, chunk, k, dl);
-        return;
-    }
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int seg = one ? 0 : g.chunk_seg[chunk];
     const int p = k * g.n_seg + seg;
     const uint32_t tau = s.pair[p].tau;
     const float c = a.c, h = a.h;
     const int o0 = threadIdx.x * 4;               // components o0..o0+3 and 1024+o0..1024+o0+3
-    float* ep = a.wp.e[k] + start + o0;
-    const float* gp = a.wp.g[k] + start + o0;
     constexpr bool kNeedW = kRule != kRuleServerMomentum || kDetach;
-    // w_t - w_prev from the last server pass's change list (unless a range
-    // of the chunk overflowed its list): the chunk's changed components are
-    // scattered into LDS, every other one is exactly +0
-    bool use_list = !kDetach && kNeedW && a.dlist != nullptr;
-    float4 u[2], gv[2], wt[2], wv[2];
-    uint32_t mw[2] = {0u, 0u};  // the mark words first, then the stream (see mark_word)
-    if (kNeedW && !use_list) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) mw[i] = mark_word(a, (int64_t)start + o0 + i * (kGroup * 4));
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        u[i] = ld4_stream(ep + i * (kGroup * 4));
-        gv[i] = ld4_stream(gp + i * (kGroup * 4));
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        wt[i] = wv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (kNeedW && !use_list) load_w4<kDetach>(a, (int64_t)start + o0 + i * (kGroup * 4), mw[i], &wt[i], &wv[i]);
-    }
-    if (use_list) {
-        const int r0 = start / kAggTopkRange, nr = (start + len - 1) / kAggTopkRange - r0 + 1;  // 1 or 2 ranges
-        int2 head0 = make_int2(0, 0), head1 = make_int2(0, 0);
-        if ((int)threadIdx.x < kWave) {
-            head0 = a.dlist[(size_t)r0 * a.dl_stride + threadIdx.x];
-            if (nr > 1) head1 = a.dlist[(size_t)(r0 + 1) * a.dl_stride + threadIdx.x];
-        }
-#pragma unroll
-        for (int i = 0; i < kChunk / kGroup; ++i) sm.dl[i * kGroup + threadIdx.x] = 0.0f;
-        if (threadIdx.x == 0) {
-            dl_cnt[0] = head0.x;
-            dl_cnt[1] = nr > 1 ? head1.x : 0;
-        }
-        __syncthreads();
-        const int32_t n0 = dl_cnt[0], n1 = dl_cnt[1];
-        use_list = n0 >= 0 && n1 >= 0;
-        if (use_list) {
-            auto put = [&](int2 en, int rr) {
-                const int j = rr * kAggTopkRange + en.x;
-                if (j >= start && j < start + len) sm.dl[j - start] = __int_as_float(en.y);
-            };
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                if (h2 >= nr) break;
-                const int32_t cnt = h2 ? n1 : n0;
-                if (threadIdx.x >= 1 && (int32_t)threadIdx.x <= cnt && (int)threadIdx.x < kWave)
-                    put(h2 ? head1 : head0, r0 + h2);
-                for (int32_t e2 = kWave + threadIdx.x; e2 <= cnt; e2 += kGroup)
-                    put(a.dlist[(size_t)(r0 + h2) * a.dl_stride + e2], r0 + h2);
-            }
-        }
-        __syncthreads();
-        if (!use_list) {  // a range's list overflowed (w_prev is then set): the marks and the two parameter vectors
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int64_t j = (int64_t)start + o0 + i * (kGroup * 4);
-                load_w4<kDetach>(a, j, mark_word(a, j), &wt[i], &wv[i]);
-            }
-        }
-    }
+    float4 u[2];
     uint32_t flags = 0;
+    if (len != kChunk) {
+        // with w_prev NULL (the last server pass updated w in place) w_t -
+        // w_prev exists only in that pass's change list, which holds whole
+        // ranges
+        const float* dl = nullptr;
+        if (kNeedW && a.w_prev == nullptr) {
+            scatter_changes(a, start, len, sm.dl, dl_cnt);
+            dl = sm.dl;
+        }
+        flags = partial_chunk<kRule, kDetach, kApprox>(a, g, s, start, len, k, tau, dl, u);
+    } else {
+        float* ep = a.wp.e[k] + start + o0;
+        const float* gp = a.wp.g[k] + start + o0;
+        const bool split = (start & 3) != 0;  // the four marks of a float4 may lie in two words
+        // w_t - w_prev from the last server pass's change list (unless a range
+        // of the chunk overflowed its list): the chunk's changed components are
+        // scattered into LDS, every other one is exactly +0
+        bool use_list = !kDetach && kNeedW && a.dlist != nullptr;
+        float4 gv[2], wt[2], wv[2];
+        uint2 mw[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};  // the mark words first, then the stream (see mark_words)
+        if (kNeedW && !use_list) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < 2; ++i) mw[i] = mark_words(a, (int64_t)start + o0 + i * (kGroup * 4), split);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            u[i] = ld4_stream(ep + i * (kGroup * 4));
+            gv[i] = ld4_stream(gp + i * (kGroup * 4));
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            wt[i] = wv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (kNeedW && !use_list) {
+                const int64_t j = (int64_t)start + o0 + i * (kGroup * 4);
+                load_w4<kDetach>(a, j, marks4(mw[i], j), &wt[i], &wv[i]);
+            }
+        }
         if (use_list) {
-            const float4 df = *reinterpret_cast<const float4*>(&sm.dl[o0 + i * (kGroup * 4)]);
-            u[i].x = rule_u_diff<kRule>(u[i].x, gv[i].x, df.x, c, h);
-            u[i].y = rule_u_diff<kRule>(u[i].y, gv[i].y, df.y, c, h);
-            u[i].z = rule_u_diff<kRule>(u[i].z, gv[i].z, df.z, c, h);
-            u[i].w = rule_u_diff<kRule>(u[i].w, gv[i].w, df.w, c, h);
-        } else {
-            u[i].x = rule_u<kRule>(u[i].x, gv[i].x, wt[i].x, wv[i].x, c, h);
-            u[i].y = rule_u<kRule>(u[i].y, gv[i].y, wt[i].y, wv[i].y, c, h);
-            u[i].z = rule_u<kRule>(u[i].z, gv[i].z, wt[i].z, wv[i].z, c, h);
-            u[i].w = rule_u<kRule>(u[i].w, gv[i].w, wt[i].w, wv[i].w, c, h);
-        }
-        st4_stream(ep + i * (kGroup * 4), u[i]);
-        if (kDetach) {
-            const float q = a.q;
-            st4_stream(a.wp.y[k] + start + o0 + i * (kGroup * 4),
-                       make_float4(detached(wt[i].x, u[i].x, q), detached(wt[i].y, u[i].y, q),
-                                   detached(wt[i].z, u[i].z, q), detached(wt[i].w, u[i].w, q)));
-        }
-        flags |= (key_of(u[i].x) >= tau ? 1u : 0u) << (i * 4 + 0);
-        flags |= (key_of(u[i].y) >= tau ? 1u : 0u) << (i * 4 + 1);
-        flags |= (key_of(u[i].z) >= tau ? 1u : 0u) << (i * 4 + 2);
-        flags |= (key_of(u[i].w) >= tau ? 1u : 0u) << (i * 4 + 3);
-    }
-    if (kApprox) {
-        const uint64_t sst = sample_state(a.seed, a.t, k);
-        float* sp = s.samp + (size_t)k * g.samp_n;
+            const int r0 = start / kAggTopkRange, nr = (start + len - 1) / kAggTopkRange - r0 + 1;  // 1 or 2 ranges
+            int2 head0 = make_int2(0, 0), head1 = make_int2(0, 0);
+            if ((int)threadIdx.x < kWave) {
+                head0 = a.dlist[(size_t)r0 * a.dl_stride + threadIdx.x];
+                if (nr > 1) head1 = a.dlist[(size_t)(r0 + 1) * a.dl_stride + threadIdx.x];
+            }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) sample_float4(sp, sst, start + o0 + i * (kGroup * 4), u[i], g.stratum, a.d);
+            for (int i = 0; i < kChunk / kGroup; ++i) sm.dl[i * kGroup + threadIdx.x] = 0.0f;
+            if (threadIdx.x == 0) {
+                dl_cnt[0] = head0.x;
+                dl_cnt[1] = nr > 1 ? head1.x : 0;
+            }
+            __syncthreads();
+            const int32_t n0 = dl_cnt[0], n1 = dl_cnt[1];
+            use_list = n0 >= 0 && n1 >= 0;
+            if (use_list) {
+                auto put = [&](int2 en, int rr) {
+                    const int j = rr * kAggTopkRange + en.x;
+                    if (j >= start && j < start + len) sm.dl[j - start] = __int_as_float(en.y);
+                };
+#pragma unroll
+                for (int h2 = 0; h2 < 2; ++h2) {
+                    if (h2 >= nr) break;
+                    const int32_t cnt = h2 ? n1 : n0;
+                    if (threadIdx.x >= 1 && (int32_t)threadIdx.x <= cnt && (int)threadIdx.x < kWave)
+                        put(h2 ? head1 : head0, r0 + h2);
+                    for (int32_t e2 = kWave + threadIdx.x; e2 <= cnt; e2 += kGroup)
+                        put(a.dlist[(size_t)(r0 + h2) * a.dl_stride + e2], r0 + h2);
+                }
+            }
+            __syncthreads();
+            if (!use_list) {  // a range's list overflowed (w_prev is then set): the marks and the two parameter vectors
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int64_t j = (int64_t)start + o0 + i * (kGroup * 4);
+                    load_w4<kDetach>(a, j, marks4(mark_words(a, j, split), j), &wt[i], &wv[i]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (use_list) {
+                const float4 df = *reinterpret_cast<const float4*>(&sm.dl[o0 + i * (kGroup * 4)]);
+                u[i].x = rule_u_diff<kRule>(u[i].x, gv[i].x, df.x, c, h);
+                u[i].y = rule_u_diff<kRule>(u[i].y, gv[i].y, df.y, c, h);
+                u[i].z = rule_u_diff<kRule>(u[i].z, gv[i].z, df.z, c, h);
+                u[i].w = rule_u_diff<kRule>(u[i].w, gv[i].w, df.w, c, h);
+            } else {
+                u[i].x = rule_u<kRule>(u[i].x, gv[i].x, wt[i].x, wv[i].x, c, h);
+                u[i].y = rule_u<kRule>(u[i].y, gv[i].y, wt[i].y, wv[i].y, c, h);
+                u[i].z = rule_u<kRule>(u[i].z, gv[i].z, wt[i].z, wv[i].z, c, h);
+                u[i].w = rule_u<kRule>(u[i].w, gv[i].w, wt[i].w, wv[i].w, c, h);
+            }
+            st4_stream(ep + i * (kGroup * 4), u[i]);
+            if (kDetach) {
+                const float q = a.q;
+                st4_stream(a.wp.y[k] + start + o0 + i * (kGroup * 4),
+                           make_float4(detached(wt[i].x, u[i].x, q), detached(wt[i].y, u[i].y, q),
+                                       detached(wt[i].z, u[i].z, q), detached(wt[i].w, u[i].w, q)));
+            }
+            flags |= (key_of(u[i].x) >= tau ? 1u : 0u) << (i * 4 + 0);
+            flags |= (key_of(u[i].y) >= tau ? 1u : 0u) << (i * 4 + 1);
+            flags |= (key_of(u[i].z) >= tau ? 1u : 0u) << (i * 4 + 2);
+            flags |= (key_of(u[i].w) >= tau ? 1u : 0u) << (i * 4 + 3);
+        }
+        if (kApprox) {
+            const uint64_t sst = sample_state(a.seed, a.t, k);
+            float* sp = s.samp + (size_t)k * g.samp_n;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) sample_float4(sp, sst, start + o0 + i * (kGroup * 4), u[i], g.stratum, a.d);
+        }
     }
     const size_t run_slot = (size_t)k * g.n_chunks + chunk;
     if (__syncthreads_or(flags != 0u) == 0) {
@@ -528,118 +608,34 @@ __global__ __launch_bounds__(kGroup) void topk_fused_vec_kernel(StepArgs a, Topk
 }
 
 
-// Element-wise pass of one wavefront over one (chunk, worker): the chunks the
-// vector path cannot take (a segment's partial last chunk, chunks with an
-// unaligned start) and the workers whose rows are not 16-byte aligned.  dl
-// (nullable, LDS): w_t - w_prev of the chunk's components (scatter_changes),
-// used instead of the two parameter vectors.
-__device__ void fused_chunk_wave(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int chunk,
-                                 int k, const float* dl) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int start = g.chunk_start[chunk];
-    const int len = g.chunk_len[chunk];
-    const int seg = g.chunk_seg[chunk];
-    const float c = a.c;
-    constexpr int kIt = kChunk / kWave;  // 32
-    const int p = k * g.n_seg + seg;
-    const uint32_t tau = s.pair[p].tau;
-    float* e = a.wp.e[k];
-    const float* gr = a.wp.g[k];
-    uint32_t flags = 0;
-    const uint64_t sst = g.approx ? sample_state(a.seed, a.t, k) : 0ull;
-#pragma unroll 4
-    for (int i = 0; i < kIt; ++i) {
-        const int o = i * kWave + lane;
-        if (o < len) {
-            const int j = start + o;
-            const float u = dl ? rule_u_diff_rt(a.rule, e[j], gr[j], dl[o], c, a.h)
-                               : rule_u_rt(a.rule, e[j], gr[j], a.w_t[j], a.w_prev[j], c, a.h);
-            e[j] = u;
-            if (a.detach) a.wp.y[k][j] = detached(a.w_t[j], u, a.q);
-            flags |= (key_of(u) >= tau ? 1u : 0u) << i;
-            if (g.approx) {
-                const int32_t q = j / g.stratum;
-                if (sample_pos(sst, q, g.stratum, a.d) == j) s.samp[(size_t)k * g.samp_n + q] = u;
-            }
-        }
-    }
-    // the chunk's slot, in index order (iteration-major, then lane)
-    const size_t run_slot = (size_t)k * g.n_chunks + chunk;
-    int2* sp = s.slot + run_slot * kChunk;
-    const uint64_t lt = lanemask_lt();
-    uint32_t base = 0;
-    for (int i = 0; i < kIt; ++i) {
-        const uint64_t b = ballot((flags >> i) & 1u);
-        if ((flags >> i) & 1u) {
-            const uint32_t q = base + popc64(b & lt);
-            const int j = start + i * kWave + lane;
-            sp[q] = make_int2(j, __float_as_int(e[j]));  // re-read of this lane's own store
-        }
-        base += popc64(b);
-    }
-    if (lane == 0) {
-        s.run_cnt[run_slot] = base;
-        if (base)
-            atomicAdd(grp_slot(s, g, a.t, k, g.chunk_cgrp[chunk], chunk), base);
-    }
-}
-
-// The element-wise kernel: one workgroup of one wavefront per (chunk,
-// worker) for the workers outside vec_mask (the vector kernel takes every
-// chunk of the others, partial ones included).
-__global__ __launch_bounds__(kWave) void topk_fused_gen_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
-                                                               uint64_t vec_mask) {
-    __shared__ float dl[kChunk];
-    __shared__ int32_t dl_cnt[2];
-    const int64_t wid = blockIdx.x;
-    if (wid >= (int64_t)g.n_chunks * g.K) return;
-    const int chunk = (int)(wid / g.K), k = (int)(wid % g.K);
-    if ((vec_mask >> k) & 1ull) return;  // the vector kernel's
-    const float* d = nullptr;
-    if (a.w_prev == nullptr) {  // w_t - w_prev from the last in-place server pass's list
-        scatter_changes(a, g.chunk_start[chunk], g.chunk_len[chunk], dl, dl_cnt);
-        d = dl;
-    }
-    fused_chunk_wave(a, g, s, chunk, k, d);
-}
-
 template <bool kApprox>
 static hipError_t launch_fused_vec_rule(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
-                                       uint64_t vec_mask, hipStream_t st) {
+                                       hipStream_t st) {
     const int grid = (int)run_order_grid(g.n_chunks, g.K, a.run);
     if (a.rule == kRuleServerMomentum) {
         if (a.detach) return hipErrorInvalidValue;  // the detached points need w_{t+1} = w_t off the sent set
         hipLaunchKernelGGL((topk_fused_vec_kernel<kRuleServerMomentum, false, kApprox>), dim3(grid), dim3(kGroup), 0,
-                           st, a, g, s, vec_mask);
+                           st, a, g, s);
     } else if (a.rule == kRuleLrInResidual) {
         if (a.detach)
             hipLaunchKernelGGL((topk_fused_vec_kernel<kRuleLrInResidual, true, kApprox>), dim3(grid), dim3(kGroup),
-                               0, st, a, g, s, vec_mask);
+                               0, st, a, g, s);
         else
             hipLaunchKernelGGL((topk_fused_vec_kernel<kRuleLrInResidual, false, kApprox>), dim3(grid), dim3(kGroup),
-                               0, st, a, g, s, vec_mask);
+                               0, st, a, g, s);
     } else {
         if (a.detach)
-            hipLaunchKernelGGL((topk_fused_vec_kernel<kRuleGmc, true, kApprox>), dim3(grid), dim3(kGroup), 0, st, a,
-                               g, s, vec_mask);
+            hipLaunchKernelGGL((topk_fused_vec_kernel<kRuleGmc, true, kApprox>), dim3(grid), dim3(kGroup), 0, st, a, g, s);
         else
             hipLaunchKernelGGL((topk_fused_vec_kernel<kRuleGmc, false, kApprox>), dim3(grid), dim3(kGroup), 0, st,
-                               a, g, s, vec_mask);
+                               a, g, s);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_topk_fused_vec(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
-                                 uint64_t vec_mask, hipStream_t st) {
-    return g.approx ? launch_fused_vec_rule<true>(a, g, s, vec_mask, st)
-                    : launch_fused_vec_rule<false>(a, g, s, vec_mask, st);
-}
-
-hipError_t launch_topk_fused_gen(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
-                                 uint64_t vec_mask, hipStream_t st) {
-    const int64_t grid = (int64_t)g.n_chunks * g.K;
-    hipLaunchKernelGGL(topk_fused_gen_kernel, dim3((unsigned)grid), dim3(kWave), 0, st, a, g, s, vec_mask);
-    return hipGetLastError();
+hipError_t launch_topk_fused_vec(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, hipStream_t st) {
+    return g.approx ? launch_fused_vec_rule<true>(a, g, s, st)
+                    : launch_fused_vec_rule<false>(a, g, s, st);
 }
 
 // ============================================================================
@@ -2065,118 +2061,38 @@ hipError_t launch_rbgs_sample(uint64_t seed, uint64_t t, int32_t nb, int32_t n_s
     return hipGetLastError();
 }
 
-// Each thread owns 4 consecutive elements per iteration; a selected block's
-// components are copied to the message at slot*B + offset (every selected
-// block but the last is full, so this is the concatenation in block order).
-__global__ __launch_bounds__(kGroup) void rbgs_fused_kernel(StepArgs a, int32_t K, int32_t B,
-                                                            const int32_t* block_slot, float* val,
-                                                            int64_t val_row, int64_t j_begin,
-                                                            uint64_t vec_mask, int64_t vec_end) {
-    const int32_t d = a.d;
-    const int64_t j0 = j_begin + ((int64_t)blockIdx.x * kGroup + threadIdx.x) * 4;
-    if (j0 >= d) return;
-    // workers in vec_mask had [0, vec_end) done by the vector kernel
-    const uint64_t skip = j0 < vec_end ? vec_mask : 0ull;
-    const float c = a.c, h = a.h, qd = a.q;
-    const int rule = a.rule;
-    const bool full = j0 + 4 <= d;
-    const bool vec = full && (B & 3) == 0 && aligned16(a.w_t) && aligned16(a.w_prev) && aligned16(val) &&
-                     (val_row & 3) == 0;
-    if (vec) {
-        const int32_t j = (int32_t)j0;
-        const int32_t b = j / B;
-        const int32_t slot = block_slot[b];
-        const float4 wt = ld4(a.w_t + j), wp = ld4(a.w_prev + j);
-        const int64_t vpos = (int64_t)slot * B + (j - (int64_t)b * B);
-        for (int k = 0; k < K; ++k) {
-            if ((skip >> k) & 1ull) continue;
-            float* e = a.wp.e[k];
-            const float* gr = a.wp.g[k];
-            float* y = a.wp.y[k];
-            if (aligned16(e) && aligned16(gr) && (!a.detach || aligned16(y))) {
-                const float4 ev = ld4(e + j), gv = ld4(gr + j);
-                float4 u;
-                u.x = rule_u_rt(rule, ev.x, gv.x, wt.x, wp.x, c, h);
-                u.y = rule_u_rt(rule, ev.y, gv.y, wt.y, wp.y, c, h);
-                u.z = rule_u_rt(rule, ev.z, gv.z, wt.z, wp.z, c, h);
-                u.w = rule_u_rt(rule, ev.w, gv.w, wt.w, wp.w, c, h);
-                if (slot >= 0) {
-                    st4(val + (size_t)k * val_row + vpos, u);
-                    st4(e + j, make_float4(u.x - u.x, u.y - u.y, u.z - u.z, u.w - u.w));
-                } else {
-                    st4(e + j, u);
-                    // unsent: e_{t+1} = u and w_{t+1} = w_t here, so this is final
-                    if (a.detach)
-                        st4(y + j, make_float4(detached(wt.x, u.x, qd), detached(wt.y, u.y, qd),
-                                               detached(wt.z, u.z, qd), detached(wt.w, u.w, qd)));
-                }
-            } else {
-                const float wtq[4] = {wt.x, wt.y, wt.z, wt.w}, wpq[4] = {wp.x, wp.y, wp.z, wp.w};
-                for (int q = 0; q < 4; ++q) {
-                    const float u = rule_u_rt(rule, e[j + q], gr[j + q], wtq[q], wpq[q], c, h);
-                    if (slot >= 0) {
-                        val[(size_t)k * val_row + vpos + q] = u;
-                        e[j + q] = u - u;
-                    } else {
-                        e[j + q] = u;
-                        if (a.detach) y[j + q] = detached(wtq[q], u, qd);
-                    }
-                }
-            }
-        }
-        return;
-    }
-    for (int q = 0; q < 4; ++q) {
-        const int64_t jj = j0 + q;
-        if (jj >= d) break;
-        const int32_t j = (int32_t)jj;
-        const int32_t b = j / B;
-        const int32_t slot = block_slot[b];
-        const float wtj = a.w_t[j], wpj = a.w_prev[j];
-        const int64_t vpos = (int64_t)slot * B + (j - (int64_t)b * B);
-        const uint64_t skip_j = j < vec_end ? vec_mask : 0ull;
-        for (int k = 0; k < K; ++k) {
-            if ((skip_j >> k) & 1ull) continue;
-            float* e = a.wp.e[k];
-            const float u = rule_u_rt(rule, e[j], a.wp.g[k][j], wtj, wpj, c, h);
-            if (slot >= 0) {
-                val[(size_t)k * val_row + vpos] = u;
-                e[j] = u - u;
-            } else {
-                e[j] = u;
-                if (a.detach) a.wp.y[k][j] = detached(wtj, u, qd);
-            }
-        }
-    }
-}
-
-// Vector path of the RBGS worker pass: one workgroup per (chunk of kChunk
-// components, worker), 8 components per thread, like the top-s pass: w_t
-// and w_prev through the cache, g, e (and the detached points) streamed.  B
-// is a multiple of 4, so each float4 lies in one block; a selected block's
-// components go to the message, the rest stay in the residual.
+// The RBGS worker pass: one workgroup per (chunk of kChunk components,
+// worker), 8 components per thread, like the top-s pass: w_t and w_prev
+// through the cache, g, e (and the detached points) streamed, at any 4-byte
+// alignment of the rows.  A float4 that lies in one block (all of them when B
+// is a multiple of 4) goes whole to the message (slot * B + offset: every
+// selected block but the last is full, so this is the concatenation in block
+// order) or stays in the residual; one that straddles blocks goes element by
+// element.
 template <int kRule, bool kDetach>
 __global__ __launch_bounds__(kGroup) void rbgs_vec_kernel(StepArgs a, int32_t K, int32_t B,
-                                                          const int32_t* block_slot, float* val, int64_t val_row,
-                                                          uint64_t vec_mask) {
+                                                          const int32_t* block_slot, float* val, int64_t val_row) {
     int chunk, k;
     run_order(blockIdx.x, K, a.run, &chunk, &k);
     const int64_t chunk0 = (int64_t)chunk * kChunk;
-    if (chunk0 >= a.d || !((vec_mask >> k) & 1ull)) return;  // padding, or the element-wise kernel's
+    if (chunk0 >= a.d) return;  // padding of the run order
+    float* vrow = val + (size_t)k * val_row;
+    // one component: u, wtj = w_t[j], its block's slot
+    auto put = [&](int64_t j, float u, float wtj, int32_t b, int32_t slot) {
+        if (slot >= 0) {
+            vrow[(int64_t)slot * B + (j - (int64_t)b * B)] = u;
+            a.wp.e[k][j] = u - u;
+        } else {
+            a.wp.e[k][j] = u;
+            // unsent: e_{t+1} = u and w_{t+1} = w_t here, so this is final
+            if (kDetach) a.wp.y[k][j] = detached(wtj, u, a.q);
+        }
+    };
     if (chunk0 + kChunk > a.d) {  // the partial last chunk, element by element
-        const float wq = a.q;
         for (int64_t j = chunk0 + threadIdx.x; j < a.d; j += kGroup) {
             const int32_t b = (int32_t)(j / B);
-            const int32_t slot = block_slot[b];
             const float wtj = a.w_t[j], wpj = a.w_prev[j];
-            const float u = rule_u<kRule>(a.wp.e[k][j], a.wp.g[k][j], wtj, wpj, a.c, a.h);
-            if (slot >= 0) {
-                val[(size_t)k * val_row + (int64_t)slot * B + (j - (int64_t)b * B)] = u;
-                a.wp.e[k][j] = u - u;
-            } else {
-                a.wp.e[k][j] = u;
-                if (kDetach) a.wp.y[k][j] = detached(wtj, u, wq);
-            }
+            put(j, rule_u<kRule>(a.wp.e[k][j], a.wp.g[k][j], wtj, wpj, a.c, a.h), wtj, b, block_slot[b]);
         }
         return;
     }
@@ -2191,27 +2107,35 @@ __global__ __launch_bounds__(kGroup) void rbgs_vec_kernel(StepArgs a, int32_t K,
     for (int i = 0; i < 2; ++i) {
         u[i] = ld4_stream(ep + i * (kGroup * 4));
         gv[i] = ld4_stream(gp + i * (kGroup * 4));
+        const int64_t j = start + i * (kGroup * 4);
         if (kNeedW)
-            load_w4<kDetach>(a, start + i * (kGroup * 4), mark_word(a, start + i * (kGroup * 4)), &wt[i], &wv[i]);
+            load_w4<kDetach>(a, j, marks4(mark_words(a, j, false), j), &wt[i], &wv[i]);
         else
             wt[i] = wv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int64_t j = start + i * (kGroup * 4);
-        const int32_t b = (int32_t)(j / B);
+        const int32_t b = (int32_t)j / B;
+        const int32_t off = (int32_t)j - b * B;
         const int32_t slot = block_slot[b];
         u[i].x = rule_u<kRule>(u[i].x, gv[i].x, wt[i].x, wv[i].x, c, h);
         u[i].y = rule_u<kRule>(u[i].y, gv[i].y, wt[i].y, wv[i].y, c, h);
         u[i].z = rule_u<kRule>(u[i].z, gv[i].z, wt[i].z, wv[i].z, c, h);
         u[i].w = rule_u<kRule>(u[i].w, gv[i].w, wt[i].w, wv[i].w, c, h);
-        if (slot >= 0) {
-            st4(val + (size_t)k * val_row + (int64_t)slot * B + (j - (int64_t)b * B), u[i]);
+        if (off + 4 > B) {  // several blocks
+            const float us[4] = {u[i].x, u[i].y, u[i].z, u[i].w}, ws[4] = {wt[i].x, wt[i].y, wt[i].z, wt[i].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int32_t bq = (int32_t)(j + q) / B;
+                put(j + q, us[q], ws[q], bq, block_slot[bq]);
+            }
+        } else if (slot >= 0) {
+            st4u(vrow + (int64_t)slot * B + off, u[i]);
             st4_stream(ep + i * (kGroup * 4),
                        make_float4(u[i].x - u[i].x, u[i].y - u[i].y, u[i].z - u[i].z, u[i].w - u[i].w));
         } else {
             st4_stream(ep + i * (kGroup * 4), u[i]);
-            // unsent: e_{t+1} = u and w_{t+1} = w_t here, so this is final
             if (kDetach) {
                 const float q = a.q;
                 st4_stream(a.wp.y[k] + j, make_float4(detached(wt[i].x, u[i].x, q), detached(wt[i].y, u[i].y, q),
@@ -2222,44 +2146,28 @@ __global__ __launch_bounds__(kGroup) void rbgs_vec_kernel(StepArgs a, int32_t K,
 }
 
 hipError_t launch_rbgs_fused(const StepArgs& a, int32_t K, int32_t B, const int32_t* block_slot,
-                             float* val, int64_t val_row, uint64_t vec_mask, hipStream_t st) {
-    // vector kernel over all chunks (the partial last one element by
-    // element) for the workers in vec_mask (B a multiple of 4 and the message
-    // rows 16-byte aligned, checked by the caller), element-wise kernel for
-    // the rest
-    const int64_t n_chunks = vec_mask ? ((int64_t)a.d + kChunk - 1) / kChunk : 0;
-    const int64_t vec_end = vec_mask ? (int64_t)a.d : 0;
-    if (n_chunks > 0) {
-        const dim3 grid((unsigned)run_order_grid(n_chunks, K, a.run));
-        if (a.rule == kRuleServerMomentum) {
-            if (a.detach) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((rbgs_vec_kernel<kRuleServerMomentum, false>), grid, dim3(kGroup), 0, st, a, K, B,
-                               block_slot, val, val_row, vec_mask);
-        } else if (a.rule == kRuleLrInResidual) {
-            if (a.detach)
-                hipLaunchKernelGGL((rbgs_vec_kernel<kRuleLrInResidual, true>), grid, dim3(kGroup), 0, st, a, K, B,
-                                   block_slot, val, val_row, vec_mask);
-            else
-                hipLaunchKernelGGL((rbgs_vec_kernel<kRuleLrInResidual, false>), grid, dim3(kGroup), 0, st, a, K, B,
-                                   block_slot, val, val_row, vec_mask);
-        } else {
-            if (a.detach)
-                hipLaunchKernelGGL((rbgs_vec_kernel<kRuleGmc, true>), grid, dim3(kGroup), 0, st, a, K, B, block_slot,
-                                   val, val_row, vec_mask);
-            else
-                hipLaunchKernelGGL((rbgs_vec_kernel<kRuleGmc, false>), grid, dim3(kGroup), 0, st, a, K, B,
-                                   block_slot, val, val_row, vec_mask);
-        }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+                             float* val, int64_t val_row, hipStream_t st) {
+    const int64_t n_chunks = ((int64_t)a.d + kChunk - 1) / kChunk;
+    const dim3 grid((unsigned)run_order_grid(n_chunks, K, a.run));
+    if (a.rule == kRuleServerMomentum) {
+        if (a.detach) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((rbgs_vec_kernel<kRuleServerMomentum, false>), grid, dim3(kGroup), 0, st, a, K, B,
+                           block_slot, val, val_row);
+    } else if (a.rule == kRuleLrInResidual) {
+        if (a.detach)
+            hipLaunchKernelGGL((rbgs_vec_kernel<kRuleLrInResidual, true>), grid, dim3(kGroup), 0, st, a, K, B,
+                               block_slot, val, val_row);
+        else
+            hipLaunchKernelGGL((rbgs_vec_kernel<kRuleLrInResidual, false>), grid, dim3(kGroup), 0, st, a, K, B,
+                               block_slot, val, val_row);
+    } else {
+        if (a.detach)
+            hipLaunchKernelGGL((rbgs_vec_kernel<kRuleGmc, true>), grid, dim3(kGroup), 0, st, a, K, B, block_slot, val,
+                               val_row);
+        else
+            hipLaunchKernelGGL((rbgs_vec_kernel<kRuleGmc, false>), grid, dim3(kGroup), 0, st, a, K, B, block_slot, val,
+                               val_row);
     }
-    const uint64_t all = K == 64 ? ~0ull : ((1ull << K) - 1ull);
-    if (vec_mask == all) return hipSuccess;
-    const int64_t j_begin = 0;
-    const int64_t threads = ((int64_t)a.d - j_begin + 3) / 4;
-    const int grid = (int)((threads + kGroup - 1) / kGroup);
-    hipLaunchKernelGGL(rbgs_fused_kernel, dim3(grid), dim3(kGroup), 0, st, a, K, B, block_slot, val, val_row,
-                       j_begin, vec_mask, vec_end);
     return hipGetLastError();
 }
 
