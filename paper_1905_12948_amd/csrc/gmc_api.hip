@@ -249,6 +249,8 @@ struct TopkTables {
     std::vector<int32_t> seg_tile_stride;
     std::vector<int2> seed_map;       // first-step sample: (segment, first run) per workgroup
     std::vector<int32_t> seg_seed_groups, seg_seed_runs, seg_seed_rank;
+    std::vector<int32_t> solo_seg, solo_small_seg, direct_seg;  // topk_solo_kernel's segments
+    int32_t solo_cap = 0, solo_small_cap = 0;
     int64_t cand_total = 0;
 };
 
@@ -296,6 +298,8 @@ TopkTables build_tables(const gmc_ctx* ctx) {
         const int64_t lc = pair_launch(ctx, n, ctx->seg_k[sg]);
         int64_t w = std::max((n + kSliceElems - 1) / kSliceElems, (lc + kSliceCands - 1) / kSliceCands);
         w = std::max<int64_t>(1, std::min<int64_t>(w, kMaxSlices));
+        const bool direct = ctx->comp != GMC_TOPK_APPROX && n <= kDirectMax;  // selected whole: no slices, no tiles
+        if (direct) w = 0;
         T.seg_slice_lo.push_back((int32_t)T.slice_seg.size());
         T.seg_slices.push_back((int32_t)w);
         for (int32_t r = 0; r < w; ++r) {
@@ -306,7 +310,7 @@ TopkTables build_tables(const gmc_ctx* ctx) {
         out += ctx->seg_k[sg];
         // copy tiles: a list of c candidates takes at most c/kTile whole
         // tiles plus a partial one per group
-        const int64_t nlaunch = (lc + kTile - 1) / kTile + rank;
+        const int64_t nlaunch = direct ? 0 : (lc + kTile - 1) / kTile + rank;
         T.seg_tile_stride.push_back((int32_t)nlaunch);
         for (int64_t i = 0; i < nlaunch; ++i) T.tile_map.push_back(make_int2(sg, (int)i));
         // first-step sample of a large segment: whole runs of kSeedRun every
@@ -323,6 +327,26 @@ TopkTables build_tables(const gmc_ctx* ctx) {
         T.seg_seed_runs.push_back((int32_t)runs);
         T.seg_seed_rank.push_back((int32_t)rank_s);
         for (int64_t gi = 0; gi < groups; ++gi) T.seed_map.push_back(make_int2(sg, (int)(gi * kSeedRunsPerGroup)));
+        if (direct) T.direct_seg.push_back(sg);
+    }
+    // topk_solo_kernel takes the others when each of them fits it; its
+    // workgroups have room for about three times k candidates (while the
+    // residual builds up a step brings up to 2.5 k)
+    bool solo = ctx->comp != GMC_TOPK_APPROX;
+    for (int sg = 0; sg < n_seg; ++sg) solo = solo && ctx->seg_k[sg] <= kSoloMaxK;
+    for (int sg = 0; solo && sg < n_seg; ++sg) {
+        if (ctx->seg_off[sg + 1] - ctx->seg_off[sg] <= kDirectMax) continue;
+        const int64_t k = ctx->seg_k[sg], list = 3 * k + 1024;
+        auto room = [&](int threads, int most) {
+            return (int32_t)std::min<int64_t>((list + threads - 1) / threads * threads, most);
+        };
+        if (k <= kSoloSmallK) {
+            T.solo_small_seg.push_back(sg);
+            T.solo_small_cap = std::max(T.solo_small_cap, room(kSoloSmallThreads, kSoloSmallCands));
+        } else {
+            T.solo_seg.push_back(sg);
+            T.solo_cap = std::max(T.solo_cap, room(kSoloThreads, kSoloCands));
+        }
     }
     for (int k = 0; k < ctx->K; ++k) {
         for (int sg = 0; sg < n_seg; ++sg) {
@@ -368,10 +392,11 @@ gmc_status prepare(gmc_ctx* ctx) {
         add(ns + 1, 4); add(ns, 4);
         add(nc, 4); add(nc, 4); add(nc, 4); add(nc, 4);
         add(ng, 4); add(ng, 4); add(ng, 4); add(ng, 4); add(ns, 4); add(ns, 4);
-        add(nsl, 4); add(nsl, 4); add(ns, 4); add(ns, 4);
+        add(nsl + 1, 4); add(nsl + 1, 4); add(ns, 4); add(ns, 4);
         add(np, 4); add(np, 4); add(np, 8);
         add(T.tile_map.size(), sizeof(int2)); add(ns, 4);
         add(T.seed_map.size() + 1, sizeof(int2)); add(ns, 4); add(ns, 4); add(ns, 4);
+        add(T.solo_seg.size() + 1, 4); add(T.solo_small_seg.size() + 1, 4); add(T.direct_seg.size() + 1, 4);
         add(np, sizeof(PairState));
         add(np * kBins, 4);
         add(np * kBins, 4);
@@ -464,6 +489,14 @@ gmc_status prepare(gmc_ctx* ctx) {
         GMC_TRY(put(T.seg_seed_groups, &g.seg_seed_groups));
         GMC_TRY(put(T.seg_seed_runs, &g.seg_seed_runs));
         GMC_TRY(put(T.seg_seed_rank, &g.seg_seed_rank));
+        g.n_solo = (int32_t)T.solo_seg.size();
+        g.n_solo_small = (int32_t)T.solo_small_seg.size();
+        g.n_direct = (int32_t)T.direct_seg.size();
+        g.solo_cap = T.solo_cap;
+        g.solo_small_cap = T.solo_small_cap;
+        GMC_TRY(put(T.solo_seg, &g.solo_seg));
+        GMC_TRY(put(T.solo_small_seg, &g.solo_small_seg));
+        GMC_TRY(put(T.direct_seg, &g.direct_seg));
         TopkScratch& sc = ctx->scr;
         sc.pair = cv.take<PairState>(np);
         std::vector<PairState> init(np);
@@ -788,7 +821,11 @@ gmc_status step_impl(gmc_ctx* ctx, const float* w_t_dev, const float* w_prev_dev
         GMC_LAUNCH(ctx, launch_topk_fused_vec(a, ctx->geo, ctx->scr, ctx->stream));
         GMC_TRY(prof_end(ctx, 0, ev));
         GMC_TRY(prof_begin(ctx, 2, &ev));
-        GMC_LAUNCH(ctx, launch_topk_compact(a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, ctx->stream));
+        if (ctx->geo.n_solo + ctx->geo.n_solo_small > 0)
+            GMC_LAUNCH(ctx, launch_topk_solo(a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, idx_dev, val_dev,
+                                             row_v, msg_len_dev, ctx->k_tot, ctx->stream));
+        GMC_LAUNCH(ctx, launch_topk_compact(a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, idx_dev, val_dev,
+                                            row_v, msg_len_dev, ctx->k_tot, ctx->stream));
         for (int pass = 2; pass <= 3; ++pass)
             GMC_LAUNCH(ctx, launch_topk_hist(pass, a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, msg_len_dev,
                                              ctx->k_tot, ctx->stream));
@@ -1146,7 +1183,10 @@ gmc_status gmc_pair_stats(gmc_ctx* ctx, int32_t* mode, int64_t* cand, int32_t n,
     std::vector<PairState> host((size_t)np);
     GMC_HIP(ctx, hipMemcpy(host.data(), ctx->scr.pair, sizeof(PairState) * (size_t)np, hipMemcpyDeviceToHost));
     for (int32_t i = 0; i < n && i < np; ++i) {
-        mode[i] = host[(size_t)i].mode == 0 ? 0 : 1;  // collected full data is the full-data path
+        // collected full data is the full-data path; so is a segment selected
+        // from u itself (done, with no candidates)
+        const PairState& ps = host[(size_t)i];
+        mode[i] = (ps.mode == 0 || (ps.mode == kModeDone && ps.cand_used > 0)) ? 0 : 1;
         cand[i] = (int64_t)host[(size_t)i].cand_used;
     }
     return GMC_OK;

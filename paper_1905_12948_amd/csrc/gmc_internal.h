@@ -72,6 +72,24 @@ constexpr int64_t kDlistMinParamBytes = int64_t(256) << 20;
 constexpr int kModeCollected = 3;
 constexpr int64_t kCollectDiv = 8;
 
+// Selection by one workgroup per pair (topk_solo_kernel): kSoloThreads threads
+// and up to kSoloCands candidates in LDS (8 bytes each beside a 16 KB histogram
+// and an 8 KB chunk table), kSoloSmallThreads and kSoloSmallCands for pairs of
+// at most kSoloSmallK kept components (several pairs per CU, cheaper
+// barriers).  A pair it has taken is marked kModeDone for the step, one it has
+// left to the other passes kModePending.  Segments of at most kDirectMax
+// components are selected from u itself (select_direct).
+constexpr int kSoloThreads = 1024;
+constexpr int kSoloSmallThreads = 256;
+constexpr int kSoloBins = 4096;
+constexpr int kSoloCands = 16 * 1024;
+constexpr int kSoloSmallCands = 4096;
+constexpr int kSoloSmallK = 1024;
+constexpr int kSoloMaxK = 15000;           // 1.04 k candidates and a few hundred still fit
+constexpr int kDirectMax = 4096;
+constexpr int kModeDone = 4;
+constexpr int kModePending = -1;
+
 // First-step threshold from a sample (topk_seed_kernel): runs of kSeedRun
 // consecutive components every kSeedStride of each segment of at least
 // kSeedMinLen components, kSeedRunsPerGroup runs per workgroup; the threshold
@@ -99,7 +117,7 @@ struct PairState {
     uint32_t tau;       // candidate threshold key of the next fused pass
     uint32_t tau_rank;  // keys at or above tau when it was set (0: not known)
     int32_t mode;       // 0 = resolve from candidates, 1 = full data, 3 = full data collected
-                        // by the second pass (kModeCollected)
+                        // by the second pass (kModeCollected), kModeDone, kModePending
     uint32_t prefix;    // radix digits fixed so far
     int32_t need;       // components still to take below the prefix
     uint32_t T;         // threshold key: k-th largest magnitude key
@@ -164,6 +182,14 @@ struct TopkGeometry {
     const int32_t* seg_seed_groups;   // [n_seg]
     const int32_t* seg_seed_runs;     // [n_seg]
     const int32_t* seg_seed_rank;     // [n_seg]
+    // topk_solo_kernel's segments (exact top-s, none unless every segment is
+    // one or direct): one workgroup of kSoloThreads / kSoloSmallThreads per
+    // (worker, segment), candidates up to solo_cap / solo_small_cap; and the
+    // direct segments, which have no tiles and no slices
+    int32_t n_solo, n_solo_small, n_direct, solo_cap, solo_small_cap;
+    const int32_t* solo_seg;          // [n_solo]
+    const int32_t* solo_small_seg;    // [n_solo_small]
+    const int32_t* direct_seg;        // [n_direct]
 };
 
 struct TopkScratch {
@@ -286,10 +312,17 @@ struct DetachArgs {
 // fused pass; pairs whose segment is not sampled keep no threshold)
 hipError_t launch_topk_seed(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, hipStream_t st);
 hipError_t launch_topk_fused_vec(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, hipStream_t st);
+// selection and message of the pairs one workgroup can take; the passes below
+// leave those
+hipError_t launch_topk_solo(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full, int margin,
+                            int32_t* idx, float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total,
+                            hipStream_t st);
 // count, then copy and the first histogram pass (the copy itself takes it
-// for the pairs of exact top-s that resolve from their candidates)
+// for the pairs of exact top-s that resolve from their candidates), and the
+// whole selection of the direct segments
 hipError_t launch_topk_compact(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full,
-                               int margin, hipStream_t st);
+                               int margin, int32_t* idx, float* val, int64_t row_len, int64_t* msg_len,
+                               int64_t msg_total, hipStream_t st);
 // passes 2 and 3 (pass 1 runs in launch_topk_compact's second kernel); pass 3
 // of exact top-s also lays out the message (per-slice offsets and msg_len),
 // the sampled-threshold top-s takes launch_topk_count for that

@@ -272,6 +272,22 @@ __device__ __forceinline__ float detached(float w, float e, float q) {
     return w - r;
 }
 
+// Inclusive prefix sum over the wavefront (DPP row shifts and broadcasts).
+__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xe, false);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xc, false);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
+// The set lanes below this one.
+__device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // Block-wide (256 threads) exclusive scan of one uint32 per thread; returns
 // the thread's exclusive prefix and writes the total to *total.
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* total, uint32_t* sh /*[kWavesPerGroup]*/) {
@@ -1211,6 +1227,7 @@ __device__ void hist_pass(const StepArgs& a, const TopkGeometry& g, const TopkSc
 
     const SliceId id = slice_id(g, blk);
     PairState* ps = &s.pair[id.p];
+    if (g.n_solo + g.n_solo_small != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
     // sampled-threshold top-s: the passes select over the sample, rank samp_r
     const bool approx = g.approx != 0;
     const int kp = approx ? g.samp_r : g.pair_k[id.p];
@@ -1393,6 +1410,7 @@ hipError_t launch_topk_hist(int pass, const StepArgs& a, const TopkGeometry& g, 
                             int force_full, int margin, int64_t* msg_len, int64_t msg_total, hipStream_t st) {
     const int grid = g.K * g.n_slices;
     if (pass != 2 && pass != 3) return hipErrorInvalidValue;  // pass 1 runs with the compaction copy
+    if (grid == 0) return hipSuccess;  // direct segments only
     if (pass == 2)
         hipLaunchKernelGGL(topk_hist_kernel<2>, dim3(grid), dim3(kGroup), 0, st, a, g, s, force_full, margin, msg_len,
                            msg_total);
@@ -1440,6 +1458,7 @@ __device__ void compact_copy(const StepArgs& a, const TopkGeometry& g, const Top
     const int seg = tm.x;
     const int p = k * g.n_seg + seg;
     PairState* ps = &s.pair[p];
+    if (g.n_solo + g.n_solo_small != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
     const uint32_t i0 = (uint32_t)tm.y;
     const uint32_t stride = (uint32_t)g.seg_tile_stride[seg];
     // the pair's groups: totals, list bases and tiles, in blocks of kGroup
@@ -1557,24 +1576,120 @@ __device__ void compact_copy(const StepArgs& a, const TopkGeometry& g, const Top
                     nullptr, nullptr, nullptr, solo);
 }
 
+// ----------------------------------------------------------------------------
+// segments of at most kDirectMax components: selected from u itself by one
+// workgroup that holds the segment in registers (component i * kGroup + t in
+// x[i]): no candidates, no threshold to keep, no fallback, and no workgroups
+// in the other passes.  T is found bit by bit (a count over the workgroup for
+// each), leaving as soon as exactly k components reach it.
+// ----------------------------------------------------------------------------
+__device__ void select_direct(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int k, int seg,
+                              int32_t* idx, float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total) {
+    __shared__ uint32_t sh[2 * kWave + 1];
+    constexpr int NT = kGroup, NW = NT / kWave, V = kDirectMax / NT;
+    static_assert(V * NW == kWave, "one (i, wavefront) count per lane of the scanning wavefront");
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
+    const int32_t lo = g.seg_start[seg], n = g.seg_start[seg + 1] - lo;
+    const int p = k * g.n_seg + seg;
+    const uint32_t kp = (uint32_t)g.pair_k[p];
+    float* e = a.wp.e[k] + lo;
+    float x[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const int o = i * NT + t;
+        const float v = e[o < n ? o : n - 1];
+        x[i] = o < n ? v : 0.0f;  // key 0 past the end: never kept before a component of the segment
+    }
+    uint32_t T = 0;
+    for (int bit = 30; bit >= 0; --bit) {
+        const uint32_t c = T | (1u << bit);
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int i = 0; i < V; ++i) cnt += popc64(ballot(key_of(x[i]) >= c));
+        uint32_t* part = sh + (bit & 1) * NW;  // the other half is still being read
+        if (lane == 0) part[wave] = cnt;
+        __syncthreads();
+        cnt = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) cnt += part[w];
+        if (cnt >= kp) T = c;
+        if (cnt == kp) break;  // exactly the kept ones reach c
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const uint64_t ba = ballot(key_of(x[i]) > T), bt = ballot(key_of(x[i]) == T);
+        if (lane == 0) sh[i * NW + wave] = (popc64(ba) << 16) | popc64(bt);  // at most 4096 each
+    }
+    __syncthreads();
+    if (wave == 0) {  // exclusive prefixes in index order, and the totals
+        const uint32_t c = sh[lane], incl = wave_scan_incl(c);
+        sh[kWave + lane] = incl - c;
+        if (lane == kWave - 1) sh[2 * kWave] = incl;
+    }
+    __syncthreads();
+    const uint32_t r = kp - (sh[2 * kWave] >> 16);  // kept at T, lowest indices first
+    constexpr int32_t R = kAggTopkRange;
+    static_assert(kDirectMax <= R, "at most one range start in a segment");
+    const int32_t off0 = (R - lo % R) % R;  // the first range start at or after the segment's start, from there
+    int32_t* irow = idx + (size_t)k * row_len + g.seg_out[seg];
+    float* vrow = val + (size_t)k * row_len + g.seg_out[seg];
+    int32_t* rp = s.rowptr + (size_t)k * (s.n_ranges + 1);
+    const int32_t row0 = g.seg_out[seg];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const uint32_t key = key_of(x[i]);
+        const uint64_t ba = ballot(key > T), bt = ballot(key == T);
+        const uint32_t pre = sh[kWave + i * NW + wave];
+        const uint32_t a_before = (pre >> 16) + mbcnt(ba), t_before = (pre & 0xffffu) + mbcnt(bt);
+        const int32_t o = i * NT + t;
+        const uint32_t q = a_before + (t_before < r ? t_before : r);
+        if (o == off0 && o < n) rp[(lo + o) / R] = row0 + (int32_t)q;
+        if (key > T || (key == T && t_before < r)) {
+            irow[q] = lo + o;
+            vrow[q] = x[i];
+            if (!a.defer_zero) e[o] = x[i] - x[i];  // residual u - C(u) at a kept component
+        }
+    }
+    if (t == 0) {
+        if (seg == g.n_seg - 1) rp[s.n_ranges] = row0 + (int32_t)kp;
+        if (seg == 0) msg_len[k] = msg_total;
+        PairState* ps = &s.pair[p];
+        ps->mode = kModeDone;
+        ps->T = T;
+        ps->r = (int32_t)r;
+        ps->cand_used = 0u;
+        atomicAdd((unsigned long long*)&s.stats[2], 1ull);
+    }
+}
+
 // The copy and the first histogram pass in one launch: the first
 // K * tiles_per_worker workgroups copy (with the first pass of the pairs that
 // resolve from their candidates), the K * n_slices after them take the first
 // pass of the others (full data, or the sample of the sampled-threshold
-// top-s); both decide which pairs those are from the groups' totals.
+// top-s); both decide which pairs those are from the groups' totals.  The last
+// K * n_direct select the direct segments, whole.
 __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
-                                                                 int force_full, int margin) {
-    const int n_copy = g.K * g.tiles_per_worker;
-    if ((int)blockIdx.x < n_copy)
-        compact_copy(a, g, s, force_full, margin, blockIdx.x);
+                                                                 int force_full, int margin, int32_t* idx, float* val,
+                                                                 int64_t row_len, int64_t* msg_len,
+                                                                 int64_t msg_total) {
+    const int n_copy = g.K * g.tiles_per_worker, n_hist = n_copy + g.K * g.n_slices;
+    const int b = blockIdx.x;
+    if (b < n_copy)
+        compact_copy(a, g, s, force_full, margin, b);
+    else if (b < n_hist)
+        hist_pass<1>(a, g, s, force_full, margin, nullptr, 0, b - n_copy);
     else
-        hist_pass<1>(a, g, s, force_full, margin, nullptr, 0, (int)blockIdx.x - n_copy);
+        select_direct(a, g, s, (b - n_hist) / g.n_direct, g.direct_seg[(b - n_hist) % g.n_direct], idx, val, row_len,
+                      msg_len, msg_total);
 }
 
 hipError_t launch_topk_compact(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full,
-                               int margin, hipStream_t st) {
-    const int64_t grid = (int64_t)g.K * g.tiles_per_worker + (int64_t)g.K * g.n_slices;
-    hipLaunchKernelGGL(topk_copy_pass1_kernel, dim3((unsigned)grid), dim3(kGroup), 0, st, a, g, s, force_full, margin);
+                               int margin, int32_t* idx, float* val, int64_t row_len, int64_t* msg_len,
+                               int64_t msg_total, hipStream_t st) {
+    const int64_t grid = (int64_t)g.K * ((int64_t)g.tiles_per_worker + g.n_slices + g.n_direct);
+    hipLaunchKernelGGL(topk_copy_pass1_kernel, dim3((unsigned)grid), dim3(kGroup), 0, st, a, g, s, force_full, margin,
+                       idx, val, row_len, msg_len, msg_total);
     return hipGetLastError();
 }
 
@@ -1681,6 +1796,7 @@ __global__ __launch_bounds__(kGroup) void topk_emit_kernel(StepArgs a, TopkGeome
     const SliceId id = slice_id(g, blockIdx.x);
     const PairState* ps = &s.pair[id.p];
     const int mode = ps->mode;
+    if (mode == kModeDone) return;  // topk_solo_kernel wrote the message
     const uint32_t T = ps->T;
     const int64_t r = ps->r;
     const size_t sl = (size_t)id.k * g.n_slices + g.seg_slice_lo[id.seg] + id.w;
@@ -1918,8 +2034,417 @@ __global__ __launch_bounds__(kGroup) void topk_emit_kernel(StepArgs a, TopkGeome
 
 hipError_t launch_topk_emit(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
                             int32_t* idx, float* val, int64_t row_len, hipStream_t st) {
+    if (g.n_slices == 0) return hipSuccess;  // direct segments only
     hipLaunchKernelGGL(topk_emit_kernel, dim3(g.K * g.n_slices), dim3(kGroup), 0, st, a, g, s, idx, val,
                        row_len);
+    return hipGetLastError();
+}
+
+// ============================================================================
+// selection and message of a whole pair in one workgroup
+//
+// A pair with few enough candidates for one workgroup's LDS needs no hand-offs
+// between workgroups: topk_solo_kernel gathers them from the chunks' slots,
+// finds the threshold and writes the message, the row pointers and the next
+// step's state in one launch, where the multi-workgroup passes above take four
+// dependent ones (copy, two histogram passes, emit), each at least a launch
+// and a last-workgroup hand-off (9-14 us even for a few thousand candidates).
+// Pairs it takes are marked kModeDone; the other passes' launches follow it
+// and their workgroups leave those pairs at once (2 us a launch).  A pair whose
+// candidates do not number between k and the room in LDS (or under
+// GMC_OPT_FORCE_FULL_SELECT) is left to them.  Only contexts whose segments
+// can all be taken use it: where some pair needs the other passes anyway, this
+// launch only adds to them (d = 11.2M per tensor, K = 4: 230 us against 202).
+// ============================================================================
+
+namespace {
+
+// A barrier for what the workgroup hands over in LDS: global loads and stores
+// stay in flight (__syncthreads also waits for the stores).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The sums of the histogram's 64 groups of 64 bins into gsum (LDS); a barrier.
+template <int NT>
+__device__ __forceinline__ void solo_groups(const uint32_t* h, uint32_t* gsum) {
+    static_assert(kSoloBins == kWave * kWave, "64 groups of 64 bins");
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = 0; i < kWave * kWave / NT; ++i) {
+        const int gr = i * (NT / kWave) + wave;
+        const uint32_t incl = wave_scan_incl(h[gr * kWave + lane]);
+        if (lane == kWave - 1) gsum[gr] = incl;
+    }
+    lds_barrier();
+}
+
+// The bin b (from the top) with above(b) < need <= above(b) + h[b], and above(b)
+// in *above_out; the bins hold at least need >= 1 keys.  One wavefront finds it,
+// from the groups' sums and then the group's bins.
+__device__ __forceinline__ uint32_t solo_find(const uint32_t* h, const uint32_t* gsum, uint32_t need,
+                                              uint32_t* above_out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    uint32_t v = gsum[kWave - 1 - lane], incl = wave_scan_incl(v);
+    uint64_t m = ballot(incl - v < need && need <= incl);
+    int l = m ? (int)__ffsll((unsigned long long)m) - 1 : 0;
+    const uint32_t gr = (uint32_t)(kWave - 1 - l);
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(incl - v), l);
+    v = h[gr * kWave + kWave - 1 - lane];
+    incl = before + wave_scan_incl(v);
+    m = ballot(incl - v < need && need <= incl);
+    l = m ? (int)__ffsll((unsigned long long)m) - 1 : 0;
+    *above_out = (uint32_t)__builtin_amdgcn_readlane((int)(incl - v), l);
+    return gr * kWave + (uint32_t)(kWave - 1 - l);
+}
+
+}  // namespace
+
+// One workgroup per (worker, solo_seg entry).  The pair's candidate list (the
+// chunks' slots one after the other) is gathered into LDS, key and index, and
+// every pass reads it there: read from the slots again for each pass it took
+// 29.5 us for 12,000 candidates, and in registers 180 KB of unrolled code.
+// One CU's instruction rate bounds the kernel, so pairs with more candidates
+// than LDS holds are better off with the multi-workgroup passes (30,000
+// candidates: 60 us here, 49 us there).
+//
+// Wavefront w takes list positions [64 w Vp, 64 (w + 1) Vp), Vp =
+// ceil(candidates / NT).  A position past the list's end holds key 0, which
+// ranks below every candidate or ties after it in list order: never kept.
+//
+// The threshold: the candidates' keys lie above tau, most within two octaves,
+// so a first histogram of 4096 bins of 2^12 keys from tau upward (its counts
+// spread over many bins: an 11-bit digit of the key would meet in a dozen)
+// finds the bin of rank k, and a second one, over that bin's keys, T itself.
+// More than k keys beyond the two octaves restart with bins of 2^19 keys.
+template <int NT>
+__global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
+                                                       const int32_t* solo_seg, int32_t n_solo, int32_t cap_list,
+                                                       int force_full, int margin, int32_t* idx, float* val,
+                                                       int64_t row_len, int64_t* msg_len, int64_t msg_total) {
+    constexpr int NW = NT / kWave;
+    extern __shared__ uint32_t dyn[];
+    uint32_t* const h = dyn;                      // [kSoloBins]
+    uint32_t* const key = dyn + kSoloBins;        // [cap_list] bits of u
+    int32_t* const lidx = reinterpret_cast<int32_t*>(key + cap_list);       // [cap_list] their indices
+    uint16_t* const cpos = reinterpret_cast<uint16_t*>(lidx + cap_list);    // [4 NT + 1] a round's chunks
+    __shared__ uint32_t wsum[2][NW], wsum2[NW], gsum[kWave], res[3];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
+    const int k = blockIdx.x / n_solo, seg = solo_seg[blockIdx.x % n_solo];
+    const int p = k * g.n_seg + seg;
+    PairState* ps = &s.pair[p];
+    const uint32_t kp = (uint32_t)g.pair_k[p], cap = (uint32_t)g.pair_cap[p];
+    const uint32_t tau = ps->tau, rank_prev = ps->tau_rank;
+    float growth = ps->growth;
+    const int g0 = g.seg_cgrp_lo[seg], ng = g.seg_cgrps[seg];
+    const int c0 = g.cgrp_lo[g0], nch = g.cgrp_hi[g0 + ng - 1] - c0;
+    const int32_t seg_lo = g.seg_start[seg], seg_hi = g.seg_start[seg + 1];
+    const uint32_t* runs = s.run_cnt + (size_t)k * g.n_chunks + c0;
+    // the pair's candidates: the sum of its groups' sub-totals
+    uint32_t C = 0;
+    {
+        const size_t nz = (size_t)g.K * g.n_cgroups;
+        const uint32_t* acc = s.grp_acc + (size_t)(a.t & 1) * kGrpSub * nz + (size_t)k * g.n_cgroups + g0;
+        for (int i = t; i < ng * kGrpSub; i += NT) C += acc[(size_t)(i / ng) * nz + i % ng];
+        const uint32_t incl = wave_scan_incl(C);
+        if (lane == kWave - 1) wsum[1][wave] = incl;
+        __syncthreads();
+        C = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) C += wsum[1][w];
+    }
+    if (force_full || C < kp || C > cap || C > (uint32_t)cap_list) {
+        if (t == 0) ps->mode = kModePending;
+        return;
+    }
+    const uint32_t Vp = (C + NT - 1) / NT;
+    const uint32_t per_wave = Vp * kWave, q0 = (uint32_t)wave * per_wave;
+    auto clear = [&](uint32_t* x, uint32_t n) {  // n a multiple of 4
+        for (uint32_t b = t; b < n / 4; b += NT) reinterpret_cast<uint4*>(x)[b] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    // gather the list, counting the first histogram on the way, in rounds of
+    // 4 NT chunks: a scan of their counts places them, sixteen lanes take the
+    // first candidates of four chunks at a time (twelve loads in flight per
+    // thread), and a wavefront the rest of a dense one (its lanes look at chunks
+    // NW apart: dense chunks come in runs)
+    uint32_t lo = tau, need = kp, sh = 12, span = (uint32_t)kSoloBins << 12;
+    uint32_t up = 0;  // this thread's keys beyond its window
+    {
+        const int2* slots = s.slot + ((size_t)k * g.n_chunks + c0) * kChunk;
+        constexpr int kRound = 4 * NT, G = 16, U = 3, N = 4, kFirst = 3 * U * G;
+        auto put = [&](uint32_t q, int2 en) {
+            const uint32_t bits = (uint32_t)en.y, kk = bits & 0x7fffffffu, dk = kk - lo;
+            key[q] = bits;
+            lidx[q] = en.x;
+            if (kk >= lo && dk < span) atomicAdd(&h[dk >> sh], 1u);
+            else if (kk >= lo) ++up;
+        };
+        uint32_t done = 0;  // candidates of the earlier rounds' chunks
+        uint32_t cnt[4];
+        auto load = [&](int b0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c = b0 + t * 4 + q;
+                const uint32_t v = runs[c < nch ? c : nch - 1];
+                cnt[q] = c < nch ? v : 0u;
+            }
+        };
+        load(0);
+        clear(h, kSoloBins);
+        if (t < (int)(Vp * NT - C)) key[C + t] = 0u;  // the last round of positions
+        for (int b0 = 0; b0 < nch; b0 += kRound) {
+            const uint32_t sum = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+            const uint32_t incl = wave_scan_incl(sum);
+            if (lane == kWave - 1) wsum2[wave] = incl;
+            __syncthreads();
+            uint32_t pos = done + incl - sum;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (w < wave) pos += wsum2[w];
+                done += wsum2[w];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                cpos[t * 4 + q] = (uint16_t)pos;
+                pos += cnt[q];
+            }
+            if (t == NT - 1) cpos[kRound] = (uint16_t)pos;
+            __syncthreads();
+            if (b0 + kRound < nch) load(b0 + kRound);
+            const int nr = nch - b0 < kRound ? nch - b0 : kRound;
+            const int2* sl = slots + (size_t)b0 * kChunk;
+            for (int cc = t / G; cc - t / G < nr; cc += N * (NT / G)) {
+                uint32_t at[N], n[N], most = 0;
+#pragma unroll
+                for (int c = 0; c < N; ++c) {
+                    const int ch = cc + c * (NT / G) < nr ? cc + c * (NT / G) : -1;
+                    at[c] = ch < 0 ? 0u : cpos[ch];
+                    n[c] = ch < 0 ? 0u : (uint32_t)cpos[ch + 1] - at[c];
+                    if (n[c] > (uint32_t)kFirst) n[c] = kFirst;
+                    most = n[c] > most ? n[c] : most;
+                }
+                for (uint32_t u0 = 0; ballot(u0 < most) != 0ull; u0 += U * G) {
+                    int2 en[N][U];
+#pragma unroll
+                    for (int c = 0; c < N; ++c) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {  // past the chunk's last: its first entry, dropped
+                            const uint32_t q = u0 + u * G + t % G;
+                            const int ch = q < n[c] ? cc + c * (NT / G) : 0;
+                            en[c][u] = sl[(size_t)ch * kChunk + (q < n[c] ? q : 0u)];
+                        }
+                    }
+#pragma unroll
+                    for (int c = 0; c < N; ++c) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const uint32_t q = u0 + u * G + t % G;
+                            if (q < n[c]) put(at[c] + q, en[c][u]);
+                        }
+                    }
+                }
+            }
+            for (int c1 = wave; c1 < nr; c1 += NT) {
+                const int cl = c1 + lane * NW;
+                const uint32_t n0 = cl < nr ? (uint32_t)cpos[cl + 1] - cpos[cl] : 0u;
+                for (uint64_t m = ballot(n0 > (uint32_t)kFirst); m != 0ull; m &= m - 1ull) {
+                    const int cc = c1 + ((int)__ffsll((unsigned long long)m) - 1) * NW;
+                    const uint32_t at = cpos[cc], n = (uint32_t)cpos[cc + 1] - at;
+                    for (uint32_t q0 = kFirst; q0 < n; q0 += 8 * kWave) {
+                        int2 en[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const uint32_t q = q0 + u * kWave + lane;
+                            en[u] = sl[(size_t)cc * kChunk + (q < n ? q : 0u)];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const uint32_t q = q0 + u * kWave + lane;
+                            if (q < n) put(at + q, en[u]);
+                        }
+                    }
+                }
+            }
+            __syncthreads();  // cpos and wsum2 are free for the next round
+        }
+    }
+    // f(key) over the wavefront's positions, in list order
+    auto each = [&](auto f) {
+        for (uint32_t i0 = 0; i0 < Vp; i0 += 4) {
+            uint32_t kk[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) kk[u] = key[q0 + (i0 + u < Vp ? i0 + u : i0) * kWave + lane];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (i0 + u >= Vp) break;
+                f(kk[u] & 0x7fffffffu);
+            }
+        }
+    };
+
+    // the threshold T: the k-th key from the top, r of the keys at T are kept
+    const uint64_t want64 = next_rank((int)kp, (int)cap, margin, C, tau, rank_prev, &growth);
+    const bool widen = want64 > (uint64_t)C;
+    uint32_t tau_next = 0, above = 0;
+    bool placed = widen;
+    {
+        const uint32_t incl = wave_scan_incl(up);
+        if (lane == kWave - 1) wsum[0][wave] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) above += wsum[0][w];
+    if (above >= need) {  // T lies beyond the window
+        lo += span;
+        sh = 19;
+        span = (uint32_t)kSoloBins << 19;
+        if (!placed && want64 > (uint64_t)above) {  // and the next threshold within it
+            placed = true;
+            tau_next = lo;
+        }
+        above = 0;
+    }
+    for (bool counted = sh == 12u;; counted = false) {
+        if (!counted) {  // the keys [lo, lo + span) in bins of 2^sh
+            lds_barrier();  // h and gsum are read
+            clear(h, kSoloBins);
+            lds_barrier();
+            each([&](uint32_t kk) {
+                const uint32_t dk = kk - lo;
+                if (kk >= lo && dk < span) atomicAdd(&h[dk >> sh], 1u);
+            });
+            lds_barrier();
+        }
+        solo_groups<NT>(h, gsum);
+        if (wave == 0) {
+            uint32_t ab;
+            if (!placed) res[2] = solo_find(h, gsum, (uint32_t)want64 - above, &ab);
+            res[0] = solo_find(h, gsum, need - above, &ab);
+            res[1] = ab;
+        }
+        lds_barrier();
+        if (!placed) {  // the next step's threshold: the floor of the bin of the key of rank want
+            placed = true;
+            tau_next = lo + (res[2] << sh);
+        }
+        lo += res[0] << sh;
+        need = need - above - res[1];
+        above = 0;
+        if (sh == 0u) break;
+        span = 1u << sh;
+        sh = sh > 12u ? sh - 12u : 0u;
+    }
+    const uint32_t T = lo, r = need;
+    if (widen) {
+        // fewer candidates than the rank aimed at: below tau by as much as its
+        // distance from T held per key
+        uint32_t step = kTauStep;
+        if (C > kp && T > tau) {
+            const float per_key = (float)(T - tau) / (float)(C - kp);
+            step = (uint32_t)fminf(per_key * (float)(want64 - (uint64_t)C) + 512.0f, (float)kTauStep);
+        }
+        tau_next = tau > step ? tau - step : 0u;
+    }
+
+    // the message, in list order; key[q] becomes the kept components before q
+    uint32_t na = 0, nt = 0;
+    each([&](uint32_t kk) {
+        na += popc64(ballot(kk > T));
+        nt += popc64(ballot(kk == T));
+    });
+    if (lane == 0) {
+        wsum[0][wave] = na;
+        wsum[1][wave] = nt;
+    }
+    __syncthreads();
+    uint32_t ab = 0, tb = 0, a_all = 0, t_all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) {
+            ab += wsum[0][w];
+            tb += wsum[1][w];
+        }
+        a_all += wsum[0][w];
+        t_all += wsum[1][w];
+    }
+    const uint32_t kept_all = a_all + (t_all < r ? t_all : r);
+    constexpr int32_t R = kAggTopkRange;
+    const int32_t row0 = g.seg_out[seg];
+    int32_t* irow = idx + (size_t)k * row_len + row0;
+    float* vrow = val + (size_t)k * row_len + row0;
+    float* e = a.wp.e[k];
+    for (uint32_t i0 = 0; i0 < Vp; i0 += 4) {
+        uint32_t bits[4];
+        int32_t j[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t q = q0 + (i0 + u < Vp ? i0 + u : i0) * kWave + lane;
+            bits[u] = key[q];
+            j[u] = lidx[q];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (i0 + u >= Vp) break;
+            const uint32_t kk = bits[u] & 0x7fffffffu;
+            const uint64_t ba = ballot(kk > T), bt = ballot(kk == T);
+            const uint32_t t_before = tb + mbcnt(bt);
+            const uint32_t o = ab + mbcnt(ba) + (t_before < r ? t_before : r);
+            ab += popc64(ba);
+            tb += popc64(bt);
+            key[q0 + (i0 + u) * kWave + lane] = o;
+            if ((kk > T || (kk == T && t_before < r)) && o < kp) {
+                const float x = __uint_as_float(bits[u]);
+                irow[o] = j[u];
+                vrow[o] = x;
+                if (!a.defer_zero) e[j[u]] = x - x;  // residual u - C(u) at a kept component
+            }
+        }
+    }
+    lds_barrier();
+    // row pointers: the kept components before the first candidate at or after
+    // each range start of the segment
+    int32_t* rp = s.rowptr + (size_t)k * (s.n_ranges + 1);
+    for (int64_t rr = ((int64_t)seg_lo + R - 1) / R + t; rr * R < seg_hi; rr += NT) {
+        uint32_t l = 0, u = C;
+        while (l < u) {
+            const uint32_t mid = (l + u) >> 1;
+            if ((int64_t)lidx[mid] < rr * R) l = mid + 1; else u = mid;
+        }
+        rp[rr] = row0 + (int32_t)(l < C ? key[l] : kept_all);
+    }
+    if (t == 0) {
+        if (seg == g.n_seg - 1) rp[s.n_ranges] = row0 + (int32_t)kept_all;
+        if (seg == 0) msg_len[k] = msg_total;
+        ps->tau_used = tau;
+        ps->tau = tau_next;
+        ps->tau_rank = (uint32_t)(want64 < 0xffffffffull ? want64 : 0xffffffffull);
+        ps->growth = growth;
+        ps->T = T;
+        ps->r = (int32_t)r;
+        ps->cand_used = C;
+        ps->mode = kModeDone;
+        if (kept_all != kp) atomicAdd((unsigned long long*)&s.stats[4], 1ull);
+        atomicAdd((unsigned long long*)&s.stats[1], 1ull);
+        atomicAdd((unsigned long long*)&s.stats[3], (unsigned long long)C);
+    }
+}
+
+hipError_t launch_topk_solo(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full, int margin,
+                            int32_t* idx, float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total,
+                            hipStream_t st) {
+    auto lds = [](int threads, int cap) { return kSoloBins * 4 + cap * 8 + (4 * threads + 2) * 2; };
+    if (g.n_solo_small)
+        hipLaunchKernelGGL(topk_solo_kernel<kSoloSmallThreads>, dim3((unsigned)(g.K * g.n_solo_small)),
+                           dim3(kSoloSmallThreads), lds(kSoloSmallThreads, g.solo_small_cap), st, a, g, s,
+                           g.solo_small_seg, g.n_solo_small, g.solo_small_cap, force_full, margin, idx, val, row_len,
+                           msg_len, msg_total);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || g.n_solo == 0) return e;
+    hipLaunchKernelGGL(topk_solo_kernel<kSoloThreads>, dim3((unsigned)(g.K * g.n_solo)), dim3(kSoloThreads),
+                       lds(kSoloThreads, g.solo_cap), st, a, g, s, g.solo_seg, g.n_solo, g.solo_cap, force_full, margin,
+                       idx, val, row_len, msg_len, msg_total);
     return hipGetLastError();
 }
 
