@@ -102,18 +102,29 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+_torch_mod = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _torch_mod = torch
+    return _torch_mod
+
+
+# The checks below run in front of every call, whose launches take 2-3 us of
+# host time each: at small sizes a call is bound by this code, so they use the
+# cheapest form of each test (is_cuda, not device.type; one pointer and a
+# stride for K rows, not K views).
 
 
 def _check(t, dtype, numel: Optional[int] = None, name: str = "tensor"):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.dtype != dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError("%s must be on a GPU device" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
@@ -122,19 +133,29 @@ def _check(t, dtype, numel: Optional[int] = None, name: str = "tensor"):
     return t.data_ptr()
 
 
-def _rows(x, d: int, K: int, name: str) -> List[int]:
+def _rows(x, d: int, K: int, name: str) -> Sequence[int]:
     """K device pointers from a [K, >=d] tensor (row stride may exceed d) or
     a sequence of K [d] tensors."""
     torch = _torch()
     if isinstance(x, torch.Tensor):
         if x.dim() != 2 or x.shape[0] != K or x.shape[1] < d:
             raise ValueError("%s must be [K, >=d]" % name)
-        if x.dtype != torch.float32 or x.device.type != "cuda" or x.stride(1) != 1:
+        if x.dtype != torch.float32 or not x.is_cuda or x.stride(1) != 1:
             raise ValueError("%s must be a float32 GPU tensor with unit inner stride" % name)
-        return [x[k].data_ptr() for k in range(K)]
+        p, step = x.data_ptr(), 4 * x.stride(0)
+        return range(p, p + K * step, step) if step else [p] * K  # 0: one row for every worker
     if len(x) != K:
         raise ValueError("%s must hold K=%d tensors" % (name, K))
     return [_check(t, torch.float32, d, "%s[%d]" % (name, k)) for k, t in enumerate(x)]
+
+
+def _raw_stream(t) -> int:
+    """torch's current stream on t's device, as a hipStream_t."""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is not None:
+        return raw(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
 
 
 def count(n: int, ratio: float) -> int:
@@ -160,7 +181,7 @@ def aggregate_static(d: int, K: int, eta: float, idx, val, msg_len, update):
     pl = _check(msg_len, torch.int64, K, "msg_len")
     pu = _check(update, torch.float32, d, "update")
     st = lib.gmc_aggregate_static(int(d), int(K), float(eta), pi, int(idx.shape[1]), pv, int(val.shape[1]), pl, pu,
-                                  ctypes.c_void_p(torch.cuda.current_stream(update.device).cuda_stream))
+                                  _raw_stream(update))
     if st != GMC_OK:
         raise GmcError(st, lib.gmc_last_error(None).decode())
 
@@ -234,6 +255,9 @@ class Gmc:
             self._call(self._lib.gmc_set_rule(self._ctx, RULES[rule]))
         if lam:
             self.set_lambda(lam)
+        self._ptrs = ctypes.c_void_p * self.K
+        # fixed once the segments, the block and the stratum are set
+        self._n_idx, self._n_val = self.K * self.index_len, self.K * self.message_len
 
     def set_eta(self, eta: float):
         """Learning rate of the following iterations (a schedule)."""
@@ -248,10 +272,13 @@ class Gmc:
         if st != GMC_OK:
             raise GmcError(st, self._lib.gmc_last_error(self._ctx).decode())
 
-    def _stream(self, device):
+    def _stream(self, t):
+        self._call(self._lib.gmc_set_stream(self._ctx, _raw_stream(t)))
+
+    def _message(self, idx, val, msg_len):
         torch = _torch()
-        s = torch.cuda.current_stream(device)
-        self._call(self._lib.gmc_set_stream(self._ctx, ctypes.c_void_p(s.cuda_stream)))
+        return (_check(idx, torch.int32, self._n_idx, "idx"), _check(val, torch.float32, self._n_val, "val"),
+                _check(msg_len, torch.int64, self.K, "msg_len"))
 
     def close(self):
         if getattr(self, "_ctx", None):
@@ -291,16 +318,14 @@ class Gmc:
         d, K = self.d, self.K
         pw = _check(w_t, torch.float32, d, "w_t")
         pp = None if w_prev is None else _check(w_prev, torch.float32, d, "w_prev")
-        gp = (ctypes.c_void_p * K)(*_rows(grads, d, K, "grads"))
-        ep = (ctypes.c_void_p * K)(*_rows(err, d, K, "err"))
-        pi = _check(idx, torch.int32, K * self.index_len, "idx")
-        pv = _check(val, torch.float32, K * self.message_len, "val")
-        pl = _check(msg_len, torch.int64, K, "msg_len")
-        self._stream(w_t.device)
+        gp = self._ptrs(*_rows(grads, d, K, "grads"))
+        ep = self._ptrs(*_rows(err, d, K, "err"))
+        pi, pv, pl = self._message(idx, val, msg_len)
+        self._stream(w_t)
         if w_k is None:
             self._call(self._lib.gmc_step(self._ctx, pw, pp, gp, ep, pi, pv, pl))
         else:
-            yp = (ctypes.c_void_p * K)(*_rows(w_k, d, K, "w_k"))
+            yp = self._ptrs(*_rows(w_k, d, K, "w_k"))
             self._call(self._lib.gmc_step_detach(self._ctx, pw, pp, gp, ep, yp, pi, pv, pl))
 
     def finish(self, idx, val, msg_len, w, w_out, w_prev=None, update=None, err=None, w_k=None):
@@ -309,18 +334,16 @@ class Gmc:
         the update and the completion of GMC+'s detached points ``w_k``."""
         torch = _torch()
         K, d = self.K, self.d
-        pi = _check(idx, torch.int32, K * self.index_len, "idx")
-        pv = _check(val, torch.float32, K * self.message_len, "val")
-        pl = _check(msg_len, torch.int64, K, "msg_len")
+        pi, pv, pl = self._message(idx, val, msg_len)
         pw = _check(w, torch.float32, d, "w")
         po = _check(w_out, torch.float32, d, "w_out")
         pp = None if w_prev is None else _check(w_prev, torch.float32, d, "w_prev")
         pu = None if update is None else _check(update, torch.float32, d, "update")
         ep = yp = None
         if w_k is not None:
-            ep = (ctypes.c_void_p * K)(*_rows(err, d, K, "err"))
-            yp = (ctypes.c_void_p * K)(*_rows(w_k, d, K, "w_k"))
-        self._stream(w.device)
+            ep = self._ptrs(*_rows(err, d, K, "err"))
+            yp = self._ptrs(*_rows(w_k, d, K, "w_k"))
+        self._stream(w)
         self._call(self._lib.gmc_finish(self._ctx, pi, pv, pl, pw, pp, po, pu, ep, yp))
 
     def iteration(self, w_t, w_prev_io, grads, err, idx, val, msg_len):
@@ -330,12 +353,10 @@ class Gmc:
         d, K = self.d, self.K
         pw = _check(w_t, torch.float32, d, "w_t")
         pp = _check(w_prev_io, torch.float32, d, "w_prev_io")
-        gp = (ctypes.c_void_p * K)(*_rows(grads, d, K, "grads"))
-        ep = (ctypes.c_void_p * K)(*_rows(err, d, K, "err"))
-        pi = _check(idx, torch.int32, K * self.index_len, "idx")
-        pv = _check(val, torch.float32, K * self.message_len, "val")
-        pl = _check(msg_len, torch.int64, K, "msg_len")
-        self._stream(w_t.device)
+        gp = self._ptrs(*_rows(grads, d, K, "grads"))
+        ep = self._ptrs(*_rows(err, d, K, "err"))
+        pi, pv, pl = self._message(idx, val, msg_len)
+        self._stream(w_t)
         self._call(self._lib.gmc_iteration(self._ctx, pw, pp, gp, ep, pi, pv, pl))
 
     def iteration_inplace(self, w, w_prev, grads, err, idx, val, msg_len):
@@ -347,12 +368,10 @@ class Gmc:
         d, K = self.d, self.K
         pw = _check(w, torch.float32, d, "w")
         pp = None if w_prev is None else _check(w_prev, torch.float32, d, "w_prev")
-        gp = (ctypes.c_void_p * K)(*_rows(grads, d, K, "grads"))
-        ep = (ctypes.c_void_p * K)(*_rows(err, d, K, "err"))
-        pi = _check(idx, torch.int32, K * self.index_len, "idx")
-        pv = _check(val, torch.float32, K * self.message_len, "val")
-        pl = _check(msg_len, torch.int64, K, "msg_len")
-        self._stream(w.device)
+        gp = self._ptrs(*_rows(grads, d, K, "grads"))
+        ep = self._ptrs(*_rows(err, d, K, "err"))
+        pi, pv, pl = self._message(idx, val, msg_len)
+        self._stream(w)
         self._call(self._lib.gmc_iteration_inplace(self._ctx, pw, pp, gp, ep, pi, pv, pl))
 
     def detach(self, w, err, w_k):
@@ -360,31 +379,27 @@ class Gmc:
         torch = _torch()
         K, d = self.K, self.d
         pw = _check(w, torch.float32, d, "w")
-        ep = (ctypes.c_void_p * K)(*_rows(err, d, K, "err"))
-        yp = (ctypes.c_void_p * K)(*_rows(w_k, d, K, "w_k"))
-        self._stream(w.device)
+        ep = self._ptrs(*_rows(err, d, K, "err"))
+        yp = self._ptrs(*_rows(w_k, d, K, "w_k"))
+        self._stream(w)
         self._call(self._lib.gmc_detach(self._ctx, pw, ep, yp))
 
     def aggregate(self, idx, val, msg_len, update):
         torch = _torch()
-        pi = _check(idx, torch.int32, self.K * self.index_len, "idx")
-        pv = _check(val, torch.float32, self.K * self.message_len, "val")
-        pl = _check(msg_len, torch.int64, self.K, "msg_len")
+        pi, pv, pl = self._message(idx, val, msg_len)
         pu = _check(update, torch.float32, self.d, "update")
-        self._stream(update.device)
+        self._stream(update)
         self._call(self._lib.gmc_aggregate(self._ctx, pi, pv, pl, pu))
 
     def aggregate_apply(self, idx, val, msg_len, w, w_out, update=None):
         """w_out = w + update (update = the server's dense update, written to
         `update` when given); w_out may be w itself."""
         torch = _torch()
-        pi = _check(idx, torch.int32, self.K * self.index_len, "idx")
-        pv = _check(val, torch.float32, self.K * self.message_len, "val")
-        pl = _check(msg_len, torch.int64, self.K, "msg_len")
+        pi, pv, pl = self._message(idx, val, msg_len)
         pw = _check(w, torch.float32, self.d, "w")
         po = _check(w_out, torch.float32, self.d, "w_out")
         pu = None if update is None else _check(update, torch.float32, self.d, "update")
-        self._stream(w.device)
+        self._stream(w)
         self._call(self._lib.gmc_aggregate_apply(self._ctx, pi, pv, pl, pw, po, pu))
 
     def apply(self, w, update, w_prev_out=None):
@@ -392,7 +407,7 @@ class Gmc:
         pw = _check(w, torch.float32, self.d, "w")
         pu = _check(update, torch.float32, self.d, "update")
         pp = None if w_prev_out is None else _check(w_prev_out, torch.float32, self.d, "w_prev_out")
-        self._stream(w.device)
+        self._stream(w)
         self._call(self._lib.gmc_apply(self._ctx, pw, pp, pu))
 
     # -- state and diagnostics ---------------------------------------------
