@@ -297,6 +297,9 @@ TopkTables build_tables(const gmc_ctx* ctx) {
         // slices of the selection passes
         const int64_t lc = pair_launch(ctx, n, ctx->seg_k[sg]);
         int64_t w = std::max((n + kSliceElems - 1) / kSliceElems, (lc + kSliceCands - 1) / kSliceCands);
+        // a small problem's slices are finer, about kSliceFill workgroups in
+        // all: a full-data pass over 110,000 components in one slice took 60 us
+        w = std::max(w, std::min((n + kSliceFine - 1) / kSliceFine, kSliceFill * n / (ctx->K * ctx->d)));
         w = std::max<int64_t>(1, std::min<int64_t>(w, kMaxSlices));
         const bool direct = ctx->comp != GMC_TOPK_APPROX && n <= kDirectMax;  // selected whole: no slices, no tiles
         if (direct) w = 0;

@@ -31,6 +31,8 @@ constexpr int kCompactChunks = 256;        // chunks per compaction group (one p
 constexpr int kGrpSub = 16;
 constexpr int kTile = kGroup * 8;          // candidates one copy workgroup moves
 constexpr int64_t kSliceElems = 1 << 19;   // full-data elements per slice (at most)
+constexpr int64_t kSliceFine = 1 << 14;    // ... and of a small problem, until
+constexpr int64_t kSliceFill = 512;        // its slices fill the GPU
 constexpr int64_t kSliceCands = 8192;      // usual candidates per slice (more when a list runs long)
 constexpr int64_t kHistSliceCands = 4096;  // candidates per second-pass workgroup (one round of loads each)
 constexpr int kMaxSlices = 256;

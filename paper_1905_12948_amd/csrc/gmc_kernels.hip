@@ -1094,7 +1094,11 @@ __device__ void finish_digit(PairState* ps, int p, uint32_t* h, uint32_t* gh, in
         // holds the key of rank `want` this step (the second pass of exact
         // top-s narrows it to 22 bits)
         float growth = growth_prev;
-        const uint64_t want64 = approx ? ((uint64_t)margin * (uint64_t)kp + 3) / 4
+        // (the sample's threshold fluctuates with the count above it; the
+        // floor of an 11-bit bin leaves some room by itself)
+        const uint64_t least = ((uint64_t)margin * (uint64_t)kp + 3) / 4;
+        const uint64_t room = (uint64_t)kp + (uint64_t)sqrtf((float)kp) + 4;
+        const uint64_t want64 = approx ? (least > room ? least : room)
                                        : next_rank(kp, g.pair_cap[p], margin, cand, tau_prev, rank_prev, &growth);
         uint32_t total, want, ab2 = 0;
         int tb;
