@@ -42,14 +42,13 @@ constexpr int kSlHist = 513;               // per slice: suffix sums of a 512-bi
 constexpr int kBins = 2048;
 constexpr int kShift1 = 20, kShift2 = 9;
 
-// Aggregation range per workgroup (RBGS), and for top-s with the number of
-// message entries one workgroup stages in LDS.
+// Aggregation range per workgroup (RBGS, and top-s), and for top-s the message
+// entries per thread of one batch (sparse messages: few entries per range on
+// average).
 constexpr int kAggRange = 2048;
 constexpr int kAggTopkRange = 4096;
-constexpr int kAggTopkStage = 512;
-// sparse messages (few entries per range on average) stage fewer, so that
-// eight workgroups fit on a CU instead of seven
-constexpr int kAggTopkStageSmall = 128;
+constexpr int kAggTopkBatch = 4;
+constexpr int kAggTopkBatchSmall = 2;
 
 constexpr uint32_t kNoThreshold = 0xffffffffu;  // no speculative candidates
 

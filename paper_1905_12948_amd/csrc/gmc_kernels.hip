@@ -288,6 +288,14 @@ __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// A barrier for what the workgroup hands over in LDS: global loads and stores
+// stay in flight (__syncthreads also waits for the stores).
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Block-wide (256 threads) exclusive scan of one uint32 per thread; returns
 // the thread's exclusive prefix and writes the total to *total.
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* total, uint32_t* sh /*[kWavesPerGroup]*/) {
@@ -1672,7 +1680,9 @@ __device__ void select_direct(const StepArgs& a, const TopkGeometry& g, const To
 // resolve from their candidates), the K * n_slices after them take the first
 // pass of the others (full data, or the sample of the sampled-threshold
 // top-s); both decide which pairs those are from the groups' totals.  The last
-// K * n_direct select the direct segments, whole.
+// K * n_direct select the direct segments, whole (kDirect: there are any; their
+// code costs the others a wavefront per SIMD).
+template <bool kDirect>
 __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
                                                                  int force_full, int margin, int32_t* idx, float* val,
                                                                  int64_t row_len, int64_t* msg_len,
@@ -1683,7 +1693,7 @@ __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, Top
         compact_copy(a, g, s, force_full, margin, b);
     else if (b < n_hist)
         hist_pass<1>(a, g, s, force_full, margin, nullptr, 0, b - n_copy);
-    else
+    else if (kDirect)
         select_direct(a, g, s, (b - n_hist) / g.n_direct, g.direct_seg[(b - n_hist) % g.n_direct], idx, val, row_len,
                       msg_len, msg_total);
 }
@@ -1692,8 +1702,12 @@ hipError_t launch_topk_compact(const StepArgs& a, const TopkGeometry& g, const T
                                int margin, int32_t* idx, float* val, int64_t row_len, int64_t* msg_len,
                                int64_t msg_total, hipStream_t st) {
     const int64_t grid = (int64_t)g.K * ((int64_t)g.tiles_per_worker + g.n_slices + g.n_direct);
-    hipLaunchKernelGGL(topk_copy_pass1_kernel, dim3((unsigned)grid), dim3(kGroup), 0, st, a, g, s, force_full, margin,
-                       idx, val, row_len, msg_len, msg_total);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kGroup), 0, st, a, g, s, force_full, margin, idx, val,
+                           row_len, msg_len, msg_total);
+    };
+    if (g.n_direct) launch(topk_copy_pass1_kernel<true>);
+    else launch(topk_copy_pass1_kernel<false>);
     return hipGetLastError();
 }
 
@@ -2062,14 +2076,6 @@ hipError_t launch_topk_emit(const StepArgs& a, const TopkGeometry& g, const Topk
 // ============================================================================
 
 namespace {
-
-// A barrier for what the workgroup hands over in LDS: global loads and stores
-// stay in flight (__syncthreads also waits for the stores).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // The sums of the histogram's 64 groups of 64 bins into gsum (LDS); a barrier.
 template <int NT>
@@ -2851,15 +2857,20 @@ hipError_t launch_agg_rowptr(int32_t K, int32_t d, const int32_t* idx, int64_t i
 
 // One workgroup per range of kAggTopkRange components (16 per thread).  The
 // workgroup first issues its loads of w_t (fused apply; a sparse apply loads
-// only the words that change) and of the previous pass's marks, then fetches the K workers' entries of the range
-// into LDS together (one round of loads) and adds them to the range's
-// accumulator one worker after the other; a range with more entries than the
-// staging holds reads them worker by worker instead.  Sent components are
-// kept as a bitmap (hb), so a workgroup needs about 22 KB of LDS (seven fit
-// on a CU) with a stage of kStage = 512 entries, 19 KB (eight) with 128 for
-// sparse messages: the kernel is bound by its chain of dependent loads, so
-// residency counts, and twice the components per chain halves the chains.
-template <bool kApply, int kStage>
+// only the words that change) and of the previous pass's marks, then takes the
+// K workers' entries of the range in batches of NB per thread, straight into
+// registers, and adds them to the range's accumulator in LDS one worker after
+// the other.  A batch is one round of loads whichever workers its entries
+// belong to: a round per worker, as every range of more than 512 entries took
+// before, made one of 600 entries from 16 workers wait 16 times (d = 25.6M,
+// K = 16, 0.1%: this kernel 34 -> 28 us in an iteration, 29 -> 22 us for the
+// dense update alone).  Sent components are kept as a bitmap (hb), so a
+// workgroup needs 19 KB of LDS (eight fit on a CU, and NB = 4 keeps the
+// registers at eight wavefronts per SIMD): the kernel is bound by its chain of
+// dependent loads, so residency counts (NB = 8, 78 registers: 34 us; the next
+// batch's loads in flight during this one's additions, 70 registers: 29 us),
+// and twice the components per chain halves the chains.
+template <bool kApply, bool kPrev, int NB>
 __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, const int32_t* idx,
                                                           int64_t idx_row, const float* val, int64_t val_row,
                                                           const int32_t* rowptr, int32_t n_ranges, FinishArgs f) {
@@ -2869,8 +2880,6 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
     __shared__ uint32_t hb[NW];  // components some worker sent
     __shared__ uint32_t wb[NW];  // marks for the next worker pass
     __shared__ uint32_t wv[NW];  // sparse apply: the words to write (old marks | sent)
-    __shared__ int32_t st_idx[kStage];
-    __shared__ float st_val[kStage];
     __shared__ int32_t src[kMaxWorkers];
     __shared__ int32_t pre[kMaxWorkers + 1];
     __shared__ uint32_t dl_n;    // entries of the change list
@@ -2899,7 +2908,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
         wx[i] = px[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (kApply && vec && !sparse) {
             wx[i] = ld4(f.w_in + base + i * (kGroup * 4) + t * 4);
-            if (f.w_prev) px[i] = ld4(f.w_prev + base + i * (kGroup * 4) + t * 4);
+            if (kPrev) px[i] = ld4(f.w_prev + base + i * (kGroup * 4) + t * 4);
         }
     }
     if (t == 0) dl_n = 0u;
@@ -2934,7 +2943,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
     // output changes: those of the previous pass's marks now, those of this
     // pass's entries as soon as the entries are staged (their loads then
     // overlap the ordered sum); a dense range's are fetched after the sum
-    const bool hb_early = sparse && vec;  // hb is complete before the sum
+    const bool hb_early = sparse && vec;
     uint32_t got = 0u;                    // bit i: wx[i] holds w_t
     if (hb_early) {
 #pragma unroll
@@ -2952,52 +2961,19 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
     }
     __syncthreads();
     const int32_t total = pre[K];
-    if (total <= kStage) {
-        for (int32_t i = t; i < total; i += kGroup) {
-            int k = 0;
-            while (i >= pre[k + 1]) ++k;
-            const int64_t q = (int64_t)src[k] + (i - pre[k]);
-            const int32_t j = idx[(size_t)k * idx_row + q];
-            const float v = val[(size_t)k * val_row + q];
-            st_idx[i] = j;
-            st_val[i] = v;
-            if (f.zero_e && j - base >= 0 && j - base < n) f.ez[k][j] = v - v;
-        }
-        __syncthreads();
-        if (hb_early) {
-            for (int32_t i = t; i < total; i += kGroup) {
-                const int64_t j = (int64_t)st_idx[i] - base;
-                if (j >= 0 && j < R) atomicOr(&hb[j >> 5], 1u << (j & 31));
-            }
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < V; ++i) {
-                const int q = i * (kGroup * 4) + t * 4;
-                if (!((got >> i) & 1u) && hb[q >> 5]) {
-                    wx[i] = ld4(f.w_in + base + q);
-                    got |= 1u << i;
-                }
-            }
-        }
-        for (int k = 0; k < K; ++k) {
-            if (pre[k + 1] > pre[k]) {
-                for (int32_t i = pre[k] + t; i < pre[k + 1]; i += kGroup) {
-                    const int64_t j = (int64_t)st_idx[i] - base;
-                    if (j >= 0 && j < R) {
-                        acc[j] = acc[j] + st_val[i];
-                        if (!hb_early) atomicOr(&hb[j >> 5], 1u << (j & 31));
-                    }
-                }
-                __syncthreads();  // worker k's additions land before worker k+1's
-            }
-        }
-    } else {
-        // a dense range (up to K entries per component): worker after
-        // worker straight from the messages, kDirect loads in flight per
-        // thread (eight with the larger stage, for dense messages: a worker
-        // sending 2048 entries of the range then takes one round trip; the
-        // sparse-message kernel keeps four and its registers)
-        constexpr int kDirect = kStage >= 512 ? 8 : 4;
+    // the range's entries, worker after worker, in batches of NB per thread:
+    // one round of loads a batch, whichever workers they belong to, then the
+    // additions worker by worker
+    const bool one_batch = total <= NB * kGroup;
+    const bool early = hb_early && one_batch;  // hb is complete before the sum
+    // (a range so dense that the batches are half as many as the workers takes a
+    // worker a round instead, with more loads per thread and no search: 12
+    // workers sending 1% of d = 11.2M, most of it in a few tensors, 31 us with
+    // batches, 29.5 so; 16 workers sending 0.1% of d = 25.6M 32.9, at a quarter
+    // of the workers 35.2, without batches 39.7)
+    const bool by_worker = 2 * total > K * NB * kGroup;
+    if (by_worker) {
+        constexpr int kDirect = 2 * NB;
         for (int k = 0; k < K; ++k) {
             const int32_t cnt = pre[k + 1] - pre[k];
             const int32_t* ip = idx + (size_t)k * idx_row + src[k];
@@ -3025,7 +3001,59 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
                     }
                 }
             }
-            __syncthreads();  // worker k's additions land before worker k+1's
+            lds_barrier();  // worker k's additions land before worker k+1's
+        }
+    }
+    int kb = 0;
+    for (int32_t b0 = by_worker ? total : 0; b0 < total; b0 += NB * kGroup) {
+        int32_t at[NB];  // worker << 16 | component of the range; -1: none
+        float v[NB];
+        while (b0 >= pre[kb + 1]) ++kb;  // the worker of the batch's first entry
+        {
+            int32_t jj[NB];
+            int k = kb;
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {  // past the last entry: the last again, dropped below
+                const int32_t i = min(b0 + u * kGroup + t, total - 1);
+                while (i >= pre[k + 1]) ++k;
+                const int32_t pos = src[k] + (i - pre[k]);
+                at[u] = k;
+                jj[u] = idx[(size_t)k * idx_row + pos];
+                v[u] = val[(size_t)k * val_row + pos];
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int64_t rel = (int64_t)jj[u] - base;
+                const bool in = b0 + u * kGroup + t < total && rel >= 0 && rel < n;
+                if (in && f.zero_e) f.ez[at[u]][jj[u]] = v[u] - v[u];
+                at[u] = in ? (at[u] << 16) | (int32_t)rel : -1;
+            }
+        }
+        if (early) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (at[u] >= 0) atomicOr(&hb[(at[u] & 0xffff) >> 5], 1u << (at[u] & 31));
+            lds_barrier();
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                const int q = i * (kGroup * 4) + t * 4;
+                if (!((got >> i) & 1u) && hb[q >> 5]) {
+                    wx[i] = ld4(f.w_in + base + q);
+                    got |= 1u << i;
+                }
+            }
+        }
+        for (int k = kb; k < K && pre[k] < b0 + NB * kGroup; ++k) {
+            if (pre[k + 1] == pre[k]) continue;
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                if ((at[u] >> 16) == k) {
+                    const int32_t j = at[u] & 0xffff;
+                    acc[j] = acc[j] + v[u];
+                    if (!early) atomicOr(&hb[j >> 5], 1u << (j & 31));
+                }
+            }
+            lds_barrier();  // worker k's additions land before worker k+1's
         }
     }
     __syncthreads();
@@ -3046,7 +3074,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
             if (kApply && (!sparse || wv[q >> 5])) {
                 const float4 x = (sparse && !((got >> i) & 1u)) ? ld4(f.w_in + base + q) : wx[i];
                 float4 nx = make_float4(x.x + dl.x, x.y + dl.y, x.z + dl.z, x.w + dl.w);
-                if (f.w_prev) {  // momentum on the server
+                if (kPrev) {  // momentum on the server
                     const float4 pp = px[i];
                     const float b = f.b;
                     nx = make_float4(nx.x + b * (x.x - pp.x), nx.y + b * (x.y - pp.y), nx.z + b * (x.z - pp.z),
@@ -3133,24 +3161,21 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
 hipError_t launch_agg_topk(int32_t K, int32_t d, const int32_t* idx, int64_t idx_row,
                            const float* val, int64_t val_row, const int32_t* rowptr,
                            int32_t n_ranges, const FinishArgs& f, hipStream_t st) {
-    // the smaller stage when the messages hold at most 48 entries per range
-    // on average (per-tensor top-s of a decoder-sized model: about 33);
-    // denser messages keep the larger one, since a range with more entries
-    // than the stage reads them worker after worker
+    // the smaller batch (fewer registers) when the messages hold at most 48
+    // entries per range on average (per-tensor top-s of a decoder-sized model:
+    // about 33), and with momentum on the server (w_{t-1} takes registers too:
+    // six wavefronts per SIMD with the larger one, 27.5 against 25.5 us at
+    // d = 11.2M, K = 4)
     const bool small = (int64_t)K * idx_row <= 48 * (int64_t)n_ranges;
-    if (f.w_out && small)
-        hipLaunchKernelGGL((agg_topk_kernel<true, kAggTopkStageSmall>), dim3(n_ranges), dim3(kGroup), 0, st, K, d,
-                           idx, idx_row, val, val_row, rowptr, n_ranges, f);
-    else if (f.w_out)
-        hipLaunchKernelGGL((agg_topk_kernel<true, kAggTopkStage>), dim3(n_ranges), dim3(kGroup), 0, st, K, d, idx,
-                           idx_row, val, val_row, rowptr, n_ranges, f);
-    else if (small)
-        hipLaunchKernelGGL((agg_topk_kernel<false, kAggTopkStageSmall>), dim3(n_ranges), dim3(kGroup), 0, st, K, d,
-                           idx, idx_row, val, val_row, rowptr, n_ranges, f);
-    else
-        hipLaunchKernelGGL((agg_topk_kernel<false, kAggTopkStage>), dim3(n_ranges), dim3(kGroup), 0, st, K, d, idx,
-                           idx_row, val, val_row, rowptr, n_ranges, f);
-    return hipGetLastError();
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(n_ranges), dim3(kGroup), 0, st, K, d, idx, idx_row, val, val_row, rowptr,
+                           n_ranges, f);
+        return hipGetLastError();
+    };
+    constexpr int B = kAggTopkBatch, S = kAggTopkBatchSmall;
+    if (f.w_out && f.w_prev) return launch(agg_topk_kernel<true, true, S>);
+    if (f.w_out) return small ? launch(agg_topk_kernel<true, false, S>) : launch(agg_topk_kernel<true, false, B>);
+    return small ? launch(agg_topk_kernel<false, false, S>) : launch(agg_topk_kernel<false, false, B>);
 }
 
 // RBGS: every worker sent the same blocks; block_slot[b] is the position q
