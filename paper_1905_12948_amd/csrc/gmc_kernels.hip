@@ -2135,7 +2135,9 @@ __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry 
                                                        int force_full, int margin, int32_t* idx, float* val,
                                                        int64_t row_len, int64_t* msg_len, int64_t msg_total) {
     constexpr int NW = NT / kWave;
-    extern __shared__ uint32_t dyn[];
+    // (the alignment is for clear(): without it the array starts right after
+    // the static arrays, off the 16 bytes its stores assume)
+    extern __shared__ __attribute__((aligned(16))) uint32_t dyn[];
     uint32_t* const h = dyn;                      // [kSoloBins]
     uint32_t* const key = dyn + kSoloBins;        // [cap_list] bits of u
     int32_t* const lidx = reinterpret_cast<int32_t*>(key + cap_list);       // [cap_list] their indices
