@@ -441,8 +441,8 @@ def main():
         stream["kernel_time_frac"] = round(stream_ms / fused_ms, 4)
         roofline["stream_ceiling"] = stream
     value = K * d / (ms_step * 1e-3) / 1e9
-    sel = {k: stats1[k] - stats0[k] for k in ("from_candidates", "full_data", "candidates", "count_errors",
-                                              "sparse_momentum_steps", "sparse_applies")}
+    sel = {k: stats1[k] - stats0[k] for k in ("from_candidates", "full_data", "whole_segments", "candidates",
+                                              "count_errors", "sparse_momentum_steps", "sparse_applies")}
     dense_bytes = survey_bytes(wl, msg_len, detach)
     out = {
         "metric": METRIC if wl.name == "resnet50" else METRIC.split(",")[0] + ", " + wl.name,

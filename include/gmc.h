@@ -430,6 +430,9 @@ gmc_status gmc_set_option(gmc_ctx* ctx, int32_t option, int64_t value);
  *       components (GMC_OPT_SPARSE_MOMENTUM)
  *   [6] server passes that wrote w_{t+1} only where their output buffer
  *       did not hold it yet (GMC_OPT_SPARSE_MOMENTUM)
+ *   [7] selections of segments of at most 4096 components by exact top-s:
+ *       these are always selected from u itself, without candidates, and
+ *       count neither in [1] nor in [2]
  */
 gmc_status gmc_stats(gmc_ctx* ctx, int64_t* out, int32_t n);
 
@@ -438,8 +441,10 @@ gmc_status gmc_stats(gmc_ctx* ctx, int64_t* out, int32_t n);
  * compressors), synchronising the context's stream first.  Pair p = k *
  * n_seg + segment; for p < min(n, K * n_seg): mode[p] = 0 when the pair's
  * top-s was resolved from its speculative candidates, 1 when it took the
- * full-data path (too few or too many candidates), and cand[p] = the
- * candidates the worker pass collected for it.  *n_pairs = K * n_seg.
+ * full-data path (too few or too many candidates, or forced), 2 when its
+ * segment is always selected whole (at most 4096 components, exact top-s;
+ * gmc_stats [7]), and cand[p] = the candidates the worker pass collected for
+ * it (0 with mode 2).  *n_pairs = K * n_seg.
  * GMC_EINVAL for RBGS, GMC_ESTATE before the first step.
  */
 gmc_status gmc_pair_stats(gmc_ctx* ctx, int32_t* mode, int64_t* cand, int32_t n, int32_t* n_pairs);
@@ -449,7 +454,9 @@ gmc_status gmc_pair_stats(gmc_ctx* ctx, int32_t* mode, int64_t* cand, int32_t n,
  * total milliseconds and timed launches since the option was last set.
  * Stages: 0 fused worker pass (RBGS: its fused gather pass), 1 not used (no
  * launches), 2 selection (RBGS: block draw),
- * 3 emit, 4 aggregate, 5 apply.  Synchronises the context's stream.
+ * 3 emit, 4 aggregate, 5 apply.  Where one workgroup selects a whole pair or
+ * segment it also writes the message, within stage 2, and stage 3 times a
+ * launch that leaves at once.  Synchronises the context's stream.
  */
 gmc_status gmc_profile_read(gmc_ctx* ctx, double* ms, int64_t* launches, int32_t n);
 

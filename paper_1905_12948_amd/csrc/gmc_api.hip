@@ -1186,11 +1186,11 @@ gmc_status gmc_pair_stats(gmc_ctx* ctx, int32_t* mode, int64_t* cand, int32_t n,
     std::vector<PairState> host((size_t)np);
     GMC_HIP(ctx, hipMemcpy(host.data(), ctx->scr.pair, sizeof(PairState) * (size_t)np, hipMemcpyDeviceToHost));
     for (int32_t i = 0; i < n && i < np; ++i) {
-        // collected full data is the full-data path; so is a segment selected
-        // from u itself (done, with no candidates)
+        // done with no candidates: a segment selected whole; collected full
+        // data is the full-data path
         const PairState& ps = host[(size_t)i];
-        mode[i] = (ps.mode == 0 || (ps.mode == kModeDone && ps.cand_used > 0)) ? 0 : 1;
-        cand[i] = (int64_t)host[(size_t)i].cand_used;
+        mode[i] = ps.mode == kModeDone ? (ps.cand_used > 0 ? 0 : 2) : ps.mode == 0 ? 0 : 1;
+        cand[i] = (int64_t)ps.cand_used;
     }
     return GMC_OK;
 }

@@ -1671,7 +1671,7 @@ __device__ void select_direct(const StepArgs& a, const TopkGeometry& g, const To
         ps->T = T;
         ps->r = (int32_t)r;
         ps->cand_used = 0u;
-        atomicAdd((unsigned long long*)&s.stats[2], 1ull);
+        atomicAdd((unsigned long long*)&s.stats[7], 1ull);
     }
 }
 

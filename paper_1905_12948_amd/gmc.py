@@ -20,6 +20,8 @@ GMC_OK, GMC_EINVAL, GMC_ENOMEM, GMC_EDEVICE, GMC_ESTATE = 0, -1, -2, -3, -4
 GMC_OPT_FORCE_FULL_SELECT, GMC_OPT_CAND_MARGIN, GMC_OPT_CAND_CAP_MULT, GMC_OPT_PROFILE = 1, 2, 3, 4
 GMC_OPT_SAMPLE_STRATUM, GMC_OPT_SPARSE_MOMENTUM, GMC_OPT_CHANGE_LIST = 5, 6, 7
 MAX_WORKERS = 64
+# gmc_profile_read's stages; "fused_gen" has no launches any more (one worker
+# kernel takes every alignment) and keeps its name for callers that list it
 STAGES = ("fused_vec", "fused_gen", "select", "emit", "aggregate", "apply")
 
 COMPRESSORS = {"topk": GMC_TOPK_GLOBAL, "topk_seg": GMC_TOPK_SEGMENTED, "rbgs": GMC_RBGS,
@@ -428,13 +430,14 @@ class Gmc:
         out = (ctypes.c_int64 * 8)()
         self._call(self._lib.gmc_stats(self._ctx, out, 8))
         keys = ("steps", "from_candidates", "full_data", "candidates", "count_errors", "sparse_momentum_steps",
-                "sparse_applies")
+                "sparse_applies", "whole_segments")
         return {k: int(out[i]) for i, k in enumerate(keys)}
 
     def pair_stats(self):
         """(mode, cand) per (worker, segment) pair of the last step, as [K, n_seg]
         int arrays: mode 0 = resolved from the speculative candidates, 1 =
-        full-data path; cand = candidates the worker pass collected."""
+        full-data path, 2 = a segment of at most 4096 components, selected
+        whole; cand = candidates the worker pass collected."""""
         import numpy as np
         np_ = ctypes.c_int32(0)
         self._call(self._lib.gmc_pair_stats(self._ctx, None, None, 0, ctypes.byref(np_)))

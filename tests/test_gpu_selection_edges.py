@@ -49,6 +49,29 @@ def test_selection_paths(sizes, ratio, hook):
                       label="%s %g %s" % (sizes, ratio, hook)), verbose=False)
 
 
+def test_segments_selected_whole_are_not_fallbacks():
+    st = run_lockstep(Case(wl([4096, 1, 300], 0.1), steps=4, iteration=True, label="whole"), verbose=False)
+    assert (st["from_candidates"], st["full_data"], st["whole_segments"]) == (0, 0, 3 * 2 * 4), st
+
+
+def test_pair_stats_tell_the_paths_apart():
+    import torch
+    from paper_1905_12948_amd import Gmc
+    K, seg = 2, [0, 4096, 4097, 104_097]
+    g = Gmc(seg[-1], K, "topk_seg", 0.01, 0.9, 0.1, segments=seg)
+    w, e = torch.zeros(seg[-1], device="cuda:0"), torch.zeros((K, seg[-1]), device="cuda:0")
+    msg = g.alloc_messages("cuda:0")
+    for _ in range(2):
+        g.iteration(w, w.clone(), torch.randn((K, seg[-1]), device="cuda:0"), e, *msg)
+    mode, cand = g.pair_stats()
+    assert mode[:, :2].tolist() == [[2, 2]] * K and not cand[:, :2].any()
+    assert (mode[:, 2] == 0).all() and (cand[:, 2] >= 1000).all()
+    g.set_option(1, 1)  # GMC_OPT_FORCE_FULL_SELECT
+    g.iteration(w, w.clone(), torch.randn((K, seg[-1]), device="cuda:0"), e, *msg)
+    mode, _ = g.pair_stats()
+    assert mode.tolist() == [[2, 2, 1]] * K
+
+
 @pytest.mark.parametrize("K,per", [(1, 0), (1, 1024), (1, 1025), (3, 341), (3, 342), (4, 512), (4, 513), (16, 33),
                                    (16, 65), (16, 600), (2, 4096), (64, 1), (64, 40)])
 def test_server_batches(K, per):
