@@ -433,6 +433,8 @@ gmc_status gmc_set_option(gmc_ctx* ctx, int32_t option, int64_t value);
  *   [7] selections of segments of at most 4096 components by exact top-s:
  *       these are always selected from u itself, without candidates, and
  *       count neither in [1] nor in [2]
+ *   [8] of [1], the selections that one workgroup made (few enough
+ *       candidates for its LDS)
  */
 gmc_status gmc_stats(gmc_ctx* ctx, int64_t* out, int32_t n);
 

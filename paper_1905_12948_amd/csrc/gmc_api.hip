@@ -95,6 +95,7 @@ struct gmc_ctx {
     void* mem = nullptr;
     size_t mem_bytes = 0;
     TopkGeometry geo{};
+    int64_t solo_wait = 0;         // steps until topk_solo_kernel is launched (solo_plan)
     TopkScratch scr{};
     int32_t* rowptr = nullptr;
     int2* dlist = nullptr;         // the last top-s server pass's change list (dl_stride per range)
@@ -249,8 +250,9 @@ struct TopkTables {
     std::vector<int32_t> seg_tile_stride;
     std::vector<int2> seed_map;       // first-step sample: (segment, first run) per workgroup
     std::vector<int32_t> seg_seed_groups, seg_seed_runs, seg_seed_rank;
-    std::vector<int32_t> solo_seg, solo_small_seg, direct_seg;  // topk_solo_kernel's segments
-    int32_t solo_cap = 0, solo_small_cap = 0;
+    std::vector<int32_t> direct_seg, solo_seg;  // selected whole; topk_solo_kernel's
+    int32_t solo_threads = 0, solo_cap = 0;
+    int64_t solo_wait = 0;            // steps before its first launch
     int64_t cand_total = 0;
 };
 
@@ -264,6 +266,46 @@ int64_t pair_capacity(const gmc_ctx* ctx, int64_t n, int64_t k) {
 constexpr int64_t kLaunchMult = 8;
 int64_t pair_launch(const gmc_ctx* ctx, int64_t n, int64_t k) {
     return std::min<int64_t>(pair_capacity(ctx, n, k), kLaunchMult * k + 2048);
+}
+
+// topk_solo_kernel's part: every segment that is not direct, or none; where it
+// takes only some pairs the four launches of the others follow in full, and
+// where it needs two launches they cost what it saves (d = 2.8M per tensor, K =
+// 4: 92 us a step with one launch of each size, 88 without, 79 with one).
+//   k: the usual candidates, 1.05-1.17 k once the residual has built up, fit in
+//   LDS up to k = 14,000.
+//   Length: the gather walks the chunks in one workgroup whatever it finds in
+//   them, 16 us less than the four launches at 300 chunks, 4 us at 1950, and 6
+//   us more at 2930 with 1024 threads; 9 us less at 390, 1 us at 780 and 14 us
+//   more at 1465 with 256 (K = 4).  So at most two chunks a thread.
+//   Steps: while the residual builds up a step brings about k (1 + 0.4 n / (k t))
+//   candidates, t steps into a run.  Where the list does not hold three times k
+//   (k > 5120) the launch would only find that and leave, 5 us of 67 at d = 2^20,
+//   K = 4, 1%, so there it waits until that many fit.
+void solo_plan(const gmc_ctx* ctx, TopkTables* T) {
+    if (ctx->comp == GMC_TOPK_APPROX) return;
+    const int n_seg = (int)ctx->seg_off.size() - 1;
+    std::vector<int32_t> seg;
+    int64_t k_most = 0, n_most = 0;
+    for (int sg = 0; sg < n_seg; ++sg) {
+        const int64_t n = ctx->seg_off[sg + 1] - ctx->seg_off[sg];
+        if (n <= kDirectMax) continue;
+        seg.push_back(sg);
+        k_most = std::max<int64_t>(k_most, ctx->seg_k[sg]);
+        n_most = std::max(n_most, n);
+    }
+    const bool small = k_most <= kSoloSmallK;
+    const int64_t threads = small ? kSoloSmallThreads : kSoloThreads;
+    if (seg.empty() || k_most > kSoloMaxK || n_most > 2 * threads * kChunk) return;
+    T->solo_seg = seg;
+    T->solo_threads = (int32_t)threads;
+    // room for three times k candidates and a little where LDS allows it
+    T->solo_cap = (int32_t)std::min<int64_t>((3 * k_most + 1024 + threads - 1) / threads * threads,
+                                             small ? kSoloSmallCands : kSoloCands);
+    for (int32_t sg : seg) {
+        const int64_t n = ctx->seg_off[sg + 1] - ctx->seg_off[sg], k = ctx->seg_k[sg], spare = T->solo_cap - k;
+        if (spare < 2 * k) T->solo_wait = std::max(T->solo_wait, (2 * n + 5 * spare - 1) / (5 * spare));
+    }
 }
 
 TopkTables build_tables(const gmc_ctx* ctx) {
@@ -332,25 +374,7 @@ TopkTables build_tables(const gmc_ctx* ctx) {
         for (int64_t gi = 0; gi < groups; ++gi) T.seed_map.push_back(make_int2(sg, (int)(gi * kSeedRunsPerGroup)));
         if (direct) T.direct_seg.push_back(sg);
     }
-    // topk_solo_kernel takes the others when each of them fits it; its
-    // workgroups have room for about three times k candidates (while the
-    // residual builds up a step brings up to 2.5 k)
-    bool solo = ctx->comp != GMC_TOPK_APPROX;
-    for (int sg = 0; sg < n_seg; ++sg) solo = solo && ctx->seg_k[sg] <= kSoloMaxK;
-    for (int sg = 0; solo && sg < n_seg; ++sg) {
-        if (ctx->seg_off[sg + 1] - ctx->seg_off[sg] <= kDirectMax) continue;
-        const int64_t k = ctx->seg_k[sg], list = 3 * k + 1024;
-        auto room = [&](int threads, int most) {
-            return (int32_t)std::min<int64_t>((list + threads - 1) / threads * threads, most);
-        };
-        if (k <= kSoloSmallK) {
-            T.solo_small_seg.push_back(sg);
-            T.solo_small_cap = std::max(T.solo_small_cap, room(kSoloSmallThreads, kSoloSmallCands));
-        } else {
-            T.solo_seg.push_back(sg);
-            T.solo_cap = std::max(T.solo_cap, room(kSoloThreads, kSoloCands));
-        }
-    }
+    solo_plan(ctx, &T);
     for (int k = 0; k < ctx->K; ++k) {
         for (int sg = 0; sg < n_seg; ++sg) {
             const int64_t n = ctx->seg_off[sg + 1] - ctx->seg_off[sg];
@@ -377,7 +401,7 @@ gmc_status prepare(gmc_ctx* ctx) {
     const int64_t samp_n = approx ? (ctx->d + ctx->stratum - 1) / ctx->stratum : 0;
     size_t bytes = 0;
     auto add = [&](size_t n, size_t sz) { bytes = ((bytes + 255) & ~(size_t)255) + n * sz; };
-    add(8, sizeof(int64_t));  // stats
+    add(kStats, sizeof(int64_t));  // stats
     add((size_t)(ctx->d + 31) / 32, 4);  // bitmap of the components the last server pass changed
     if (ctx->comp == GMC_RBGS) {
         add((size_t)(ctx->nb + 31) / 32, 4);
@@ -399,7 +423,7 @@ gmc_status prepare(gmc_ctx* ctx) {
         add(np, 4); add(np, 4); add(np, 8);
         add(T.tile_map.size(), sizeof(int2)); add(ns, 4);
         add(T.seed_map.size() + 1, sizeof(int2)); add(ns, 4); add(ns, 4); add(ns, 4);
-        add(T.solo_seg.size() + 1, 4); add(T.solo_small_seg.size() + 1, 4); add(T.direct_seg.size() + 1, 4);
+        add(T.solo_seg.size() + 1, 4); add(T.direct_seg.size() + 1, 4);
         add(np, sizeof(PairState));
         add(np * kBins, 4);
         add(np * kBins, 4);
@@ -425,7 +449,7 @@ gmc_status prepare(gmc_ctx* ctx) {
     ctx->mem_bytes = bytes;
     GMC_HIP(ctx, hipMemset(mem, 0, bytes));
     Carver cv{reinterpret_cast<char*>(mem)};
-    ctx->stats = cv.take<int64_t>(8);
+    ctx->stats = cv.take<int64_t>(kStats);
     ctx->wbits = cv.take<uint32_t>((size_t)(ctx->d + 31) / 32);
     ctx->wbits_valid = false;
     ctx->wbits_pair = false;
@@ -493,12 +517,11 @@ gmc_status prepare(gmc_ctx* ctx) {
         GMC_TRY(put(T.seg_seed_runs, &g.seg_seed_runs));
         GMC_TRY(put(T.seg_seed_rank, &g.seg_seed_rank));
         g.n_solo = (int32_t)T.solo_seg.size();
-        g.n_solo_small = (int32_t)T.solo_small_seg.size();
         g.n_direct = (int32_t)T.direct_seg.size();
         g.solo_cap = T.solo_cap;
-        g.solo_small_cap = T.solo_small_cap;
+        g.solo_threads = T.solo_threads;
+        ctx->solo_wait = T.solo_wait;
         GMC_TRY(put(T.solo_seg, &g.solo_seg));
-        GMC_TRY(put(T.solo_small_seg, &g.solo_small_seg));
         GMC_TRY(put(T.direct_seg, &g.direct_seg));
         TopkScratch& sc = ctx->scr;
         sc.pair = cv.take<PairState>(np);
@@ -824,19 +847,25 @@ gmc_status step_impl(gmc_ctx* ctx, const float* w_t_dev, const float* w_prev_dev
         GMC_LAUNCH(ctx, launch_topk_fused_vec(a, ctx->geo, ctx->scr, ctx->stream));
         GMC_TRY(prof_end(ctx, 0, ev));
         GMC_TRY(prof_begin(ctx, 2, &ev));
-        if (ctx->geo.n_solo + ctx->geo.n_solo_small > 0)
-            GMC_LAUNCH(ctx, launch_topk_solo(a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, idx_dev, val_dev,
-                                             row_v, msg_len_dev, ctx->k_tot, ctx->stream));
-        GMC_LAUNCH(ctx, launch_topk_compact(a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, idx_dev, val_dev,
+        // a step without the one-workgroup launch runs the other passes on a
+        // geometry without its segments, so that they look at no pair's mark
+        // of an earlier step (a captured step may be replayed after later ones)
+        TopkGeometry geo = ctx->geo;
+        if (ctx->force_full || ctx->solo_wait > 0) geo.n_solo = 0;
+        if (ctx->solo_wait > 0) --ctx->solo_wait;
+        if (geo.n_solo > 0)
+            GMC_LAUNCH(ctx, launch_topk_solo(a, geo, ctx->scr, ctx->margin, idx_dev, val_dev, row_v, msg_len_dev,
+                                             ctx->k_tot, ctx->stream));
+        GMC_LAUNCH(ctx, launch_topk_compact(a, geo, ctx->scr, ctx->force_full, ctx->margin, idx_dev, val_dev,
                                             row_v, msg_len_dev, ctx->k_tot, ctx->stream));
         for (int pass = 2; pass <= 3; ++pass)
-            GMC_LAUNCH(ctx, launch_topk_hist(pass, a, ctx->geo, ctx->scr, ctx->force_full, ctx->margin, msg_len_dev,
+            GMC_LAUNCH(ctx, launch_topk_hist(pass, a, geo, ctx->scr, ctx->force_full, ctx->margin, msg_len_dev,
                                              ctx->k_tot, ctx->stream));
         if (ctx->comp == GMC_TOPK_APPROX)  // exact top-s counts in the third pass
-            GMC_LAUNCH(ctx, launch_topk_count(a, ctx->geo, ctx->scr, msg_len_dev, ctx->k_tot, ctx->stream));
+            GMC_LAUNCH(ctx, launch_topk_count(a, geo, ctx->scr, msg_len_dev, ctx->k_tot, ctx->stream));
         GMC_TRY(prof_end(ctx, 2, ev));
         GMC_TRY(prof_begin(ctx, 3, &ev));
-        GMC_LAUNCH(ctx, launch_topk_emit(a, ctx->geo, ctx->scr, idx_dev, val_dev, row_v, ctx->stream));
+        GMC_LAUNCH(ctx, launch_topk_emit(a, geo, ctx->scr, idx_dev, val_dev, row_v, ctx->stream));
         GMC_TRY(prof_end(ctx, 3, ev));
     }
     ctx->t += 1;
@@ -1165,12 +1194,12 @@ gmc_status gmc_stats(gmc_ctx* ctx, int64_t* out, int32_t n) {
     if (!ctx || !out || n < 0) return fail(ctx, GMC_EINVAL, "gmc_stats: bad argument");
     GMC_HIP(ctx, hipSetDevice(ctx->device));
     GMC_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    int64_t host[8] = {0};
+    int64_t host[kStats] = {0};
     if (ctx->stats) GMC_HIP(ctx, hipMemcpy(host, ctx->stats, sizeof host, hipMemcpyDeviceToHost));
     host[0] = ctx->t;
     host[5] = ctx->sparse_steps;
     host[6] = ctx->sparse_applies;
-    for (int32_t i = 0; i < n && i < 8; ++i) out[i] = host[i];
+    for (int32_t i = 0; i < n && i < kStats; ++i) out[i] = host[i];
     return GMC_OK;
 }
 

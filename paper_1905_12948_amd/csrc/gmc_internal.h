@@ -50,6 +50,8 @@ constexpr int kAggTopkRange = 4096;
 constexpr int kAggTopkBatch = 4;
 constexpr int kAggTopkBatchSmall = 2;
 
+constexpr int kStats = 9;  // gmc_stats
+
 constexpr uint32_t kNoThreshold = 0xffffffffu;  // no speculative candidates
 
 // The components a top-s server pass changed, per range of kAggTopkRange:
@@ -75,8 +77,8 @@ constexpr int64_t kCollectDiv = 8;
 
 // Selection by one workgroup per pair (topk_solo_kernel): kSoloThreads threads
 // and up to kSoloCands candidates in LDS (8 bytes each beside a 16 KB histogram
-// and an 8 KB chunk table), kSoloSmallThreads and kSoloSmallCands for pairs of
-// at most kSoloSmallK kept components (several pairs per CU, cheaper
+// and a table of two chunks per thread), kSoloSmallThreads and kSoloSmallCands
+// where no pair keeps more than kSoloSmallK (several pairs per CU, cheaper
 // barriers).  A pair it has taken is marked kModeDone for the step, one it has
 // left to the other passes kModePending.  Segments of at most kDirectMax
 // components are selected from u itself (select_direct).
@@ -86,7 +88,7 @@ constexpr int kSoloBins = 4096;
 constexpr int kSoloCands = 16 * 1024;
 constexpr int kSoloSmallCands = 4096;
 constexpr int kSoloSmallK = 1024;
-constexpr int kSoloMaxK = 15000;           // 1.04 k candidates and a few hundred still fit
+constexpr int kSoloMaxK = 14000;           // the 1.05-1.17 k candidates of a steady state fit
 constexpr int kDirectMax = 4096;
 constexpr int kModeDone = 4;
 constexpr int kModePending = -1;
@@ -183,13 +185,12 @@ struct TopkGeometry {
     const int32_t* seg_seed_groups;   // [n_seg]
     const int32_t* seg_seed_runs;     // [n_seg]
     const int32_t* seg_seed_rank;     // [n_seg]
-    // topk_solo_kernel's segments (exact top-s, none unless every segment is
-    // one or direct): one workgroup of kSoloThreads / kSoloSmallThreads per
-    // (worker, segment), candidates up to solo_cap / solo_small_cap; and the
-    // direct segments, which have no tiles and no slices
-    int32_t n_solo, n_solo_small, n_direct, solo_cap, solo_small_cap;
+    // topk_solo_kernel's segments (all that are not direct, or none; none too
+    // in a step that does not launch it): one workgroup of solo_threads per
+    // (worker, segment), candidates up to solo_cap; and the direct segments,
+    // which have no tiles and no slices
+    int32_t n_solo, n_direct, solo_threads, solo_cap;
     const int32_t* solo_seg;          // [n_solo]
-    const int32_t* solo_small_seg;    // [n_solo_small]
     const int32_t* direct_seg;        // [n_direct]
 };
 
@@ -217,7 +218,7 @@ struct TopkScratch {
     float* samp;                  // [K][samp_n] the sample's values (sampled-threshold top-s)
     int32_t* rowptr;              // [K][n_ranges+1] server-pass row pointers, also written by the emit
     int32_t n_ranges;             // ranges of kAggTopkRange components
-    int64_t* stats;               // [8]
+    int64_t* stats;               // [kStats] (gmc_stats)
 };
 
 struct StepArgs {
@@ -315,9 +316,8 @@ hipError_t launch_topk_seed(const StepArgs& a, const TopkGeometry& g, const Topk
 hipError_t launch_topk_fused_vec(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, hipStream_t st);
 // selection and message of the pairs one workgroup can take; the passes below
 // leave those
-hipError_t launch_topk_solo(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full, int margin,
-                            int32_t* idx, float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total,
-                            hipStream_t st);
+hipError_t launch_topk_solo(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int margin, int32_t* idx,
+                            float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total, hipStream_t st);
 // count, then copy and the first histogram pass (the copy itself takes it
 // for the pairs of exact top-s that resolve from their candidates), and the
 // whole selection of the direct segments

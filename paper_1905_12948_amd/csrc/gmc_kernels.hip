@@ -1239,7 +1239,7 @@ __device__ void hist_pass(const StepArgs& a, const TopkGeometry& g, const TopkSc
 
     const SliceId id = slice_id(g, blk);
     PairState* ps = &s.pair[id.p];
-    if (g.n_solo + g.n_solo_small != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
+    if (g.n_solo != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
     // sampled-threshold top-s: the passes select over the sample, rank samp_r
     const bool approx = g.approx != 0;
     const int kp = approx ? g.samp_r : g.pair_k[id.p];
@@ -1470,7 +1470,7 @@ __device__ void compact_copy(const StepArgs& a, const TopkGeometry& g, const Top
     const int seg = tm.x;
     const int p = k * g.n_seg + seg;
     PairState* ps = &s.pair[p];
-    if (g.n_solo + g.n_solo_small != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
+    if (g.n_solo != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
     const uint32_t i0 = (uint32_t)tm.y;
     const uint32_t stride = (uint32_t)g.seg_tile_stride[seg];
     // the pair's groups: totals, list bases and tiles, in blocks of kGroup
@@ -2069,10 +2069,8 @@ hipError_t launch_topk_emit(const StepArgs& a, const TopkGeometry& g, const Topk
 // and a last-workgroup hand-off (9-14 us even for a few thousand candidates).
 // Pairs it takes are marked kModeDone; the other passes' launches follow it
 // and their workgroups leave those pairs at once (2 us a launch).  A pair whose
-// candidates do not number between k and the room in LDS (or under
-// GMC_OPT_FORCE_FULL_SELECT) is left to them.  Only contexts whose segments
-// can all be taken use it: where some pair needs the other passes anyway, this
-// launch only adds to them (d = 11.2M per tensor, K = 4: 230 us against 202).
+// candidates do not number between k and the room in LDS is left to them.
+// Which contexts launch it, and from which step on: solo_plan.
 // ============================================================================
 
 namespace {
@@ -2113,7 +2111,7 @@ __device__ __forceinline__ uint32_t solo_find(const uint32_t* h, const uint32_t*
 }  // namespace
 
 // One workgroup per (worker, solo_seg entry).  The pair's candidate list (the
-// chunks' slots one after the other) is gathered into LDS, key and index, and
+// slots of at most 2 NT chunks, one after the other) is gathered into LDS, key and index, and
 // every pass reads it there: read from the slots again for each pass it took
 // 29.5 us for 12,000 candidates, and in registers 180 KB of unrolled code.
 // One CU's instruction rate bounds the kernel, so pairs with more candidates
@@ -2132,8 +2130,8 @@ __device__ __forceinline__ uint32_t solo_find(const uint32_t* h, const uint32_t*
 template <int NT>
 __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
                                                        const int32_t* solo_seg, int32_t n_solo, int32_t cap_list,
-                                                       int force_full, int margin, int32_t* idx, float* val,
-                                                       int64_t row_len, int64_t* msg_len, int64_t msg_total) {
+                                                       int margin, int32_t* idx, float* val, int64_t row_len,
+                                                       int64_t* msg_len, int64_t msg_total) {
     constexpr int NW = NT / kWave;
     // (the alignment is for clear(): without it the array starts right after
     // the static arrays, off the 16 bytes its stores assume)
@@ -2141,8 +2139,8 @@ __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry 
     uint32_t* const h = dyn;                      // [kSoloBins]
     uint32_t* const key = dyn + kSoloBins;        // [cap_list] bits of u
     int32_t* const lidx = reinterpret_cast<int32_t*>(key + cap_list);       // [cap_list] their indices
-    uint16_t* const cpos = reinterpret_cast<uint16_t*>(lidx + cap_list);    // [4 NT + 1] a round's chunks
-    __shared__ uint32_t wsum[2][NW], wsum2[NW], gsum[kWave], res[3];
+    uint16_t* const cpos = reinterpret_cast<uint16_t*>(lidx + cap_list);    // [2 NT + 1] the chunks' first positions
+    __shared__ uint32_t wsum[2][NW], gsum[kWave], res[3];
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
     const int k = blockIdx.x / n_solo, seg = solo_seg[blockIdx.x % n_solo];
     const int p = k * g.n_seg + seg;
@@ -2167,7 +2165,7 @@ __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry 
 #pragma unroll
         for (int w = 0; w < NW; ++w) C += wsum[1][w];
     }
-    if (force_full || C < kp || C > cap || C > (uint32_t)cap_list) {
+    if (C < kp || C > cap || C > (uint32_t)cap_list) {
         if (t == 0) ps->mode = kModePending;
         return;
     }
@@ -2176,16 +2174,16 @@ __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry 
     auto clear = [&](uint32_t* x, uint32_t n) {  // n a multiple of 4
         for (uint32_t b = t; b < n / 4; b += NT) reinterpret_cast<uint4*>(x)[b] = make_uint4(0u, 0u, 0u, 0u);
     };
-    // gather the list, counting the first histogram on the way, in rounds of
-    // 4 NT chunks: a scan of their counts places them, sixteen lanes take the
-    // first candidates of four chunks at a time (twelve loads in flight per
-    // thread), and a wavefront the rest of a dense one (its lanes look at chunks
-    // NW apart: dense chunks come in runs)
+    // gather the list, counting the first histogram on the way: a scan of the
+    // chunks' counts places them, sixteen lanes take the first candidates of
+    // four chunks at a time (twelve loads in flight per thread), and a wavefront
+    // the rest of a dense one (its lanes look at chunks NW apart: dense chunks
+    // come in runs)
     uint32_t lo = tau, need = kp, sh = 12, span = (uint32_t)kSoloBins << 12;
     uint32_t up = 0;  // this thread's keys beyond its window
     {
-        const int2* slots = s.slot + ((size_t)k * g.n_chunks + c0) * kChunk;
-        constexpr int kRound = 4 * NT, G = 16, U = 3, N = 4, kFirst = 3 * U * G;
+        const int2* sl = s.slot + ((size_t)k * g.n_chunks + c0) * kChunk;
+        constexpr int G = 16, U = 3, N = 4, kFirst = 3 * U * G;
         auto put = [&](uint32_t q, int2 en) {
             const uint32_t bits = (uint32_t)en.y, kk = bits & 0x7fffffffu, dk = kk - lo;
             key[q] = bits;
@@ -2193,94 +2191,79 @@ __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry 
             if (kk >= lo && dk < span) atomicAdd(&h[dk >> sh], 1u);
             else if (kk >= lo) ++up;
         };
-        uint32_t done = 0;  // candidates of the earlier rounds' chunks
-        uint32_t cnt[4];
-        auto load = [&](int b0) {
+        uint32_t cnt[2];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c = b0 + t * 4 + q;
-                const uint32_t v = runs[c < nch ? c : nch - 1];
-                cnt[q] = c < nch ? v : 0u;
-            }
-        };
-        load(0);
+        for (int q = 0; q < 2; ++q) {
+            const int c = t * 2 + q;
+            const uint32_t v = runs[c < nch ? c : nch - 1];
+            cnt[q] = c < nch ? v : 0u;
+        }
         clear(h, kSoloBins);
         if (t < (int)(Vp * NT - C)) key[C + t] = 0u;  // the last round of positions
-        for (int b0 = 0; b0 < nch; b0 += kRound) {
-            const uint32_t sum = cnt[0] + cnt[1] + cnt[2] + cnt[3];
-            const uint32_t incl = wave_scan_incl(sum);
-            if (lane == kWave - 1) wsum2[wave] = incl;
-            __syncthreads();
-            uint32_t pos = done + incl - sum;
+        const uint32_t incl = wave_scan_incl(cnt[0] + cnt[1]);
+        if (lane == kWave - 1) wsum[0][wave] = incl;
+        __syncthreads();
+        uint32_t pos = incl - cnt[0] - cnt[1];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                if (w < wave) pos += wsum2[w];
-                done += wsum2[w];
-            }
+        for (int w = 0; w < NW; ++w)
+            if (w < wave) pos += wsum[0][w];
+        cpos[t * 2] = (uint16_t)pos;
+        cpos[t * 2 + 1] = (uint16_t)(pos + cnt[0]);
+        if (t == NT - 1) cpos[2 * NT] = (uint16_t)(pos + cnt[0] + cnt[1]);
+        __syncthreads();
+        for (int cc = t / G; cc - t / G < nch; cc += N * (NT / G)) {
+            uint32_t at[N], n[N], most = 0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                cpos[t * 4 + q] = (uint16_t)pos;
-                pos += cnt[q];
+            for (int c = 0; c < N; ++c) {
+                const int ch = cc + c * (NT / G) < nch ? cc + c * (NT / G) : -1;
+                at[c] = ch < 0 ? 0u : cpos[ch];
+                n[c] = ch < 0 ? 0u : (uint32_t)cpos[ch + 1] - at[c];
+                if (n[c] > (uint32_t)kFirst) n[c] = kFirst;
+                most = n[c] > most ? n[c] : most;
             }
-            if (t == NT - 1) cpos[kRound] = (uint16_t)pos;
-            __syncthreads();
-            if (b0 + kRound < nch) load(b0 + kRound);
-            const int nr = nch - b0 < kRound ? nch - b0 : kRound;
-            const int2* sl = slots + (size_t)b0 * kChunk;
-            for (int cc = t / G; cc - t / G < nr; cc += N * (NT / G)) {
-                uint32_t at[N], n[N], most = 0;
+            for (uint32_t u0 = 0; ballot(u0 < most) != 0ull; u0 += U * G) {
+                int2 en[N][U];
 #pragma unroll
                 for (int c = 0; c < N; ++c) {
-                    const int ch = cc + c * (NT / G) < nr ? cc + c * (NT / G) : -1;
-                    at[c] = ch < 0 ? 0u : cpos[ch];
-                    n[c] = ch < 0 ? 0u : (uint32_t)cpos[ch + 1] - at[c];
-                    if (n[c] > (uint32_t)kFirst) n[c] = kFirst;
-                    most = n[c] > most ? n[c] : most;
-                }
-                for (uint32_t u0 = 0; ballot(u0 < most) != 0ull; u0 += U * G) {
-                    int2 en[N][U];
 #pragma unroll
-                    for (int c = 0; c < N; ++c) {
-#pragma unroll
-                        for (int u = 0; u < U; ++u) {  // past the chunk's last: its first entry, dropped
-                            const uint32_t q = u0 + u * G + t % G;
-                            const int ch = q < n[c] ? cc + c * (NT / G) : 0;
-                            en[c][u] = sl[(size_t)ch * kChunk + (q < n[c] ? q : 0u)];
-                        }
+                    for (int u = 0; u < U; ++u) {  // past the chunk's last: the first chunk's first entry, dropped
+                        const uint32_t q = u0 + u * G + t % G;
+                        const int ch = q < n[c] ? cc + c * (NT / G) : 0;
+                        en[c][u] = sl[(size_t)ch * kChunk + (q < n[c] ? q : 0u)];
                     }
+                }
 #pragma unroll
-                    for (int c = 0; c < N; ++c) {
+                for (int c = 0; c < N; ++c) {
 #pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            const uint32_t q = u0 + u * G + t % G;
-                            if (q < n[c]) put(at[c] + q, en[c][u]);
-                        }
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t q = u0 + u * G + t % G;
+                        if (q < n[c]) put(at[c] + q, en[c][u]);
                     }
                 }
             }
-            for (int c1 = wave; c1 < nr; c1 += NT) {
-                const int cl = c1 + lane * NW;
-                const uint32_t n0 = cl < nr ? (uint32_t)cpos[cl + 1] - cpos[cl] : 0u;
-                for (uint64_t m = ballot(n0 > (uint32_t)kFirst); m != 0ull; m &= m - 1ull) {
-                    const int cc = c1 + ((int)__ffsll((unsigned long long)m) - 1) * NW;
-                    const uint32_t at = cpos[cc], n = (uint32_t)cpos[cc + 1] - at;
-                    for (uint32_t q0 = kFirst; q0 < n; q0 += 8 * kWave) {
-                        int2 en[8];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const uint32_t q = q0 + u * kWave + lane;
-                            en[u] = sl[(size_t)cc * kChunk + (q < n ? q : 0u)];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const uint32_t q = q0 + u * kWave + lane;
-                            if (q < n) put(at + q, en[u]);
-                        }
-                    }
-                }
-            }
-            __syncthreads();  // cpos and wsum2 are free for the next round
         }
+        for (int c1 = wave; c1 < nch; c1 += NT) {
+            const int cl = c1 + lane * NW;
+            const uint32_t n0 = cl < nch ? (uint32_t)cpos[cl + 1] - cpos[cl] : 0u;
+            for (uint64_t m = ballot(n0 > (uint32_t)kFirst); m != 0ull; m &= m - 1ull) {
+                const int cc = c1 + ((int)__ffsll((unsigned long long)m) - 1) * NW;
+                const uint32_t at = cpos[cc], n = (uint32_t)cpos[cc + 1] - at;
+                for (uint32_t q0 = kFirst; q0 < n; q0 += 8 * kWave) {
+                    int2 en[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t q = q0 + u * kWave + lane;
+                        en[u] = sl[(size_t)cc * kChunk + (q < n ? q : 0u)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t q = q0 + u * kWave + lane;
+                        if (q < n) put(at + q, en[u]);
+                    }
+                }
+            }
+        }
+        __syncthreads();
     }
     // f(key) over the wavefront's positions, in list order
     auto each = [&](auto f) {
@@ -2440,24 +2423,20 @@ __global__ __launch_bounds__(NT) void topk_solo_kernel(StepArgs a, TopkGeometry 
         if (kept_all != kp) atomicAdd((unsigned long long*)&s.stats[4], 1ull);
         atomicAdd((unsigned long long*)&s.stats[1], 1ull);
         atomicAdd((unsigned long long*)&s.stats[3], (unsigned long long)C);
+        atomicAdd((unsigned long long*)&s.stats[8], 1ull);
     }
 }
 
-hipError_t launch_topk_solo(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full, int margin,
-                            int32_t* idx, float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total,
-                            hipStream_t st) {
-    auto lds = [](int threads, int cap) { return kSoloBins * 4 + cap * 8 + (4 * threads + 2) * 2; };
-    if (g.n_solo_small)
-        hipLaunchKernelGGL(topk_solo_kernel<kSoloSmallThreads>, dim3((unsigned)(g.K * g.n_solo_small)),
-                           dim3(kSoloSmallThreads), lds(kSoloSmallThreads, g.solo_small_cap), st, a, g, s,
-                           g.solo_small_seg, g.n_solo_small, g.solo_small_cap, force_full, margin, idx, val, row_len,
-                           msg_len, msg_total);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || g.n_solo == 0) return e;
-    hipLaunchKernelGGL(topk_solo_kernel<kSoloThreads>, dim3((unsigned)(g.K * g.n_solo)), dim3(kSoloThreads),
-                       lds(kSoloThreads, g.solo_cap), st, a, g, s, g.solo_seg, g.n_solo, g.solo_cap, force_full, margin,
-                       idx, val, row_len, msg_len, msg_total);
-    return hipGetLastError();
+hipError_t launch_topk_solo(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int margin, int32_t* idx,
+                            float* val, int64_t row_len, int64_t* msg_len, int64_t msg_total, hipStream_t st) {
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(g.K * g.n_solo)), dim3(threads),
+                           kSoloBins * 4 + g.solo_cap * 8 + (2 * threads + 2) * 2, st, a, g, s, g.solo_seg, g.n_solo,
+                           g.solo_cap, margin, idx, val, row_len, msg_len, msg_total);
+        return hipGetLastError();
+    };
+    return g.solo_threads == kSoloSmallThreads ? launch(topk_solo_kernel<kSoloSmallThreads>, kSoloSmallThreads)
+                                               : launch(topk_solo_kernel<kSoloThreads>, kSoloThreads);
 }
 
 // ============================================================================

@@ -427,10 +427,10 @@ class Gmc:
         self._call(self._lib.gmc_set_option(self._ctx, int(option), int(value)))
 
     def stats(self) -> dict:
-        out = (ctypes.c_int64 * 8)()
-        self._call(self._lib.gmc_stats(self._ctx, out, 8))
+        out = (ctypes.c_int64 * 9)()
+        self._call(self._lib.gmc_stats(self._ctx, out, 9))
         keys = ("steps", "from_candidates", "full_data", "candidates", "count_errors", "sparse_momentum_steps",
-                "sparse_applies", "whole_segments")
+                "sparse_applies", "whole_segments", "one_workgroup")
         return {k: int(out[i]) for i, k in enumerate(keys)}
 
     def pair_stats(self):

@@ -1,6 +1,6 @@
 """The selection at the edges of its paths: segments at and around the size
 selected whole (4096), pairs at and around the sizes one workgroup takes (k =
-1024 and 15,000), ties, zeros and non-finite values in them, candidates
+1024 and 14,000, 512 and 2048 chunks of 2048), ties, zeros and non-finite values in them, candidates
 crowded into a few chunks; and the server pass at and around its batch sizes.
 Everything against the oracle (or the sum in worker order), bit for bit."""
 import dataclasses
@@ -36,17 +36,70 @@ HOOKS = {
 
 
 @pytest.mark.parametrize("hook", sorted(HOOKS))
-@pytest.mark.parametrize("sizes,ratio", [
-    ([4096, 4097, 1, 2, 255, 8192, 4095], 0.1),      # whole segments beside others
-    ([1, 4096, 257], 1.0),                            # whole segments only, all kept
-    ([102_400], 0.01),                                # k = 1024: the smaller workgroup's largest
-    ([102_401], 0.01),                                # k = 1025
-    ([50_000, 6000], 0.3),                            # k = 15,000 beside a small pair
-    ([50_001, 6000], 0.3),                            # k = 15,001: the multi-workgroup passes
+@pytest.mark.parametrize("sizes,ratio,solo", [
+    ([4096, 4097, 1, 2, 255, 8192, 4095], 0.1, True),  # whole segments beside others
+    ([1, 4096, 257], 1.0, False),                       # whole segments only, all kept
+    ([102_400], 0.01, True),                            # k = 1024: the smaller workgroup's largest
+    ([102_401], 0.01, True),                            # k = 1025
+    ([46_666, 6000], 0.3, True),                        # k = 14,000 beside a small pair, in one launch
+    ([46_667, 6000], 0.3, False),                       # k = 14,001: the multi-workgroup passes
+    ([50_000, 6000], 0.3, False),
 ])
-def test_selection_paths(sizes, ratio, hook):
-    run_lockstep(Case(wl(sizes, ratio), steps=4, iteration=True, sparse_w=True, grad_hook=HOOKS[hook],
-                      label="%s %g %s" % (sizes, ratio, hook)), verbose=False)
+def test_selection_paths(sizes, ratio, solo, hook):
+    """solo: one workgroup takes the pairs once their candidates fit, within
+    twelve steps of an undisturbed run."""
+    st = run_lockstep(Case(wl(sizes, ratio), steps=12, iteration=True, sparse_w=True, grad_hook=HOOKS[hook],
+                           label="%s %g %s" % (sizes, ratio, hook)), verbose=False)
+    assert st["one_workgroup"] > 0 if solo and hook == "plain" else st["one_workgroup"] == 0 or solo, st
+
+
+@pytest.mark.parametrize("n,ratio,solo", [(2 * 256 * 2048, 0.0009, True), (2 * 256 * 2048 + 1, 0.0009, False),
+                                          (2 * 1024 * 2048, 0.0005, True), (2 * 1024 * 2048 + 1, 0.0005, False)])
+def test_longest_segments_of_one_workgroup(n, ratio, solo):
+    """Two chunks a thread, and one component more.  From step 3 on the
+    gradients are small, so the residual stands still and the candidates fit."""
+    st = run_lockstep(Case(wl([n], ratio, comp="topk"), steps=7, iteration=True, sparse_w=True,
+                           grad_hook=lambda t, g: g if t < 3 else g * np.float32(1e-4), label="n %d" % n),
+                      check_every=3, verbose=False)
+    assert (st["one_workgroup"] > 0) == solo, st
+
+
+@pytest.mark.parametrize("sizes,ratio", [([4097], 0.2), ([6000], 0.3)])
+def test_candidates_far_above_the_threshold(sizes, ratio):
+    """Half of the gradients a thousand times larger from one step to the next:
+    more than k candidates lie over two octaves above the threshold that
+    collected them, beyond the first histogram, in lists that fit."""
+    def jump(t, g):
+        return g if t < 2 else (g * np.where(np.arange(g.shape[1]) % 2, 1, 1000)).astype(np.float32)
+    st = run_lockstep(Case(wl(sizes, ratio), steps=3, iteration=True, grad_hook=jump, label="jump"), verbose=False)
+    assert st["one_workgroup"] == 2 * 2, st  # steps 1 and 2; step 0 has no threshold
+
+
+def test_steps_with_and_without_the_one_workgroup_launch():
+    """k = 10,000: the launch waits for ceil(0.4 n / (16,384 - k)) = 3 steps,
+    and forced full-data steps do without it; neither it nor its marks of an
+    earlier step change what a step sends."""
+    import torch
+    from paper_1905_12948_amd import Gmc
+    d, K = 33_333, 2
+    grads = torch.randn((4, K, d), device="cuda:0")
+
+    def run(force):
+        g = Gmc(d, K, "topk", 0.3, 0.9, 0.1)
+        w, wp, e = (torch.zeros(s, device="cuda:0") for s in (d, d, (K, d)))
+        msg, out, one = g.alloc_messages("cuda:0"), [], []
+        for t in range(24):
+            g.set_option(1, int(force(t)))  # GMC_OPT_FORCE_FULL_SELECT
+            g.iteration(w, wp, grads[t % 4], e, *msg)
+            w, wp = wp, w
+            out.append([x.clone() for x in (w, e, *msg)])
+            one.append(g.stats()["one_workgroup"])
+        return out, np.diff([0] + one)
+    want, none = run(lambda t: True)
+    got, one = run(lambda t: t % 5 == 4)
+    assert not none.any() and not one[:3].any() and not one[4::5].any() and one[10:].sum() > 0, one
+    for t, (x, y) in enumerate(zip(got, want)):
+        assert all(torch.equal(p, q) for p, q in zip(x, y)), t
 
 
 def test_segments_selected_whole_are_not_fallbacks():
