@@ -1239,7 +1239,11 @@ __device__ void hist_pass(const StepArgs& a, const TopkGeometry& g, const TopkSc
 
     const SliceId id = slice_id(g, blk);
     PairState* ps = &s.pair[id.p];
-    if (g.n_solo != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
+    // topk_solo_kernel wrote the message.  The first pass needs no look at the
+    // mark: such a pair's candidates number between k and the capacity, so it
+    // leaves below (and the look costs topk_copy_pass1_kernel<false> a register
+    // too many)
+    if (PASS != 1 && g.n_solo != 0 && ps->mode == kModeDone) return;
     // sampled-threshold top-s: the passes select over the sample, rank samp_r
     const bool approx = g.approx != 0;
     const int kp = approx ? g.samp_r : g.pair_k[id.p];
@@ -1680,8 +1684,11 @@ __device__ void select_direct(const StepArgs& a, const TopkGeometry& g, const To
 // resolve from their candidates), the K * n_slices after them take the first
 // pass of the others (full data, or the sample of the sampled-threshold
 // top-s); both decide which pairs those are from the groups' totals.  The last
-// K * n_direct select the direct segments, whole (kDirect: there are any; their
-// code costs the others a wavefront per SIMD).
+// K * n_direct select the direct segments, whole (kDirect: there are any).  The
+// copy keeps its workgroups resident, seven wavefronts per SIMD by LDS, with 72
+// registers (kDirect false); the direct segments' code brings it to 76, six
+// wavefronts.  With six the copy of a context without direct segments took 21.8
+// us for 21.5 (d = 25.6M, K = 16, 0.1%), 13.7 for 13.6 (K = 4, 0.01%).
 template <bool kDirect>
 __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
                                                                  int force_full, int margin, int32_t* idx, float* val,
@@ -1691,7 +1698,7 @@ __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, Top
     const int b = blockIdx.x;
     if (b < n_copy)
         compact_copy(a, g, s, force_full, margin, b);
-    else if (b < n_hist)
+    else if (!kDirect || b < n_hist)
         hist_pass<1>(a, g, s, force_full, margin, nullptr, 0, b - n_copy);
     else if (kDirect)
         select_direct(a, g, s, (b - n_hist) / g.n_direct, g.direct_seg[(b - n_hist) % g.n_direct], idx, val, row_len,

@@ -48,3 +48,10 @@ def test_dynamic_lds_of_the_one_workgroup_selection_is_16_byte_aligned(kernels):
     # its dynamic array follows the static ones and is cleared with 16-byte stores
     for k in named(kernels, "topk_solo_kernel"):
         assert k[".group_segment_fixed_size"] % 16 == 0, (k[".name"], k[".group_segment_fixed_size"])
+
+
+def test_the_copy_keeps_seven_wavefronts_per_simd(kernels):
+    # 512 registers per lane and SIMD, allocated by eights; no scratch
+    for k in named(kernels, "topk_copy_pass1_kernelILb0E"):
+        assert k[".vgpr_count"] <= 72 and k[".private_segment_fixed_size"] == 0, k[".vgpr_count"]
+        assert 7 * k[".group_segment_fixed_size"] <= 160 * 1024
