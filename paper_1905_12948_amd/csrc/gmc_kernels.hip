@@ -2849,14 +2849,22 @@ hipError_t launch_agg_rowptr(int32_t K, int32_t d, const int32_t* idx, int64_t i
 // K workers' entries of the range in batches of NB per thread, straight into
 // registers, and adds them to the range's accumulator in LDS one worker after
 // the other.  A batch is one round of loads whichever workers its entries
-// belong to: a round per worker, as every range of more than 512 entries took
-// before, made one of 600 entries from 16 workers wait 16 times (d = 25.6M,
-// K = 16, 0.1%: this kernel 34 -> 28 us in an iteration, 29 -> 22 us for the
-// dense update alone).  Sent components are kept as a bitmap (hb), so a
+// belong to: a round per worker makes a range of 600 entries from 16 workers
+// wait 16 times (ResNet-50's tensors, K = 16, 0.1%: this kernel 41.6 -> 30.8 us
+// in a steady iteration, 33.2 -> 22.0 us for the dense update alone).  A last
+// batch of at most one entry a thread is one predicated round, so that a
+// sparse range loads its entries and no more, and the workers of the entries
+// are found from their first positions, one per lane, read by scalar: with
+// every thread's NB loads whatever the range held, and a chain of LDS reads
+// for each worker, messages spread evenly (d = 25.6M, K = 16, 0.1%) took 39.0
+// us for the dense update and 56.7 in an iteration, 29.2 and 50.8 so.  (Eight
+// workers' 0.1% of a decoder's tensors are the exception, 190.8 us with those
+// and 198.8 so, 204.6 with a round per worker.)
+// Sent components are kept as a bitmap (hb), so a
 // workgroup needs 19 KB of LDS (eight fit on a CU, and NB = 4 keeps the
 // registers at eight wavefronts per SIMD): the kernel is bound by its chain of
 // dependent loads, so residency counts (NB = 8, 78 registers: 34 us; the next
-// batch's loads in flight during this one's additions, 70 registers: 29 us),
+// batch's loads in flight during this one's additions, 70 registers: 29 us; of 28),
 // and twice the components per chain halves the chains.
 template <bool kApply, bool kPrev, int NB>
 __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, const int32_t* idx,
@@ -2929,8 +2937,9 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
     for (int q = t; q < R; q += kGroup) acc[q] = 0.0f;
     // sparse apply: w_t is fetched only in the 32-component words the
     // output changes: those of the previous pass's marks now, those of this
-    // pass's entries as soon as the entries are staged (their loads then
-    // overlap the ordered sum); a dense range's are fetched after the sum
+    // pass's entries as soon as the entries are there (their loads then
+    // overlap the ordered sum), where one batch holds them all; otherwise
+    // after the sum
     const bool hb_early = sparse && vec;
     uint32_t got = 0u;                    // bit i: wx[i] holds w_t
     if (hb_early) {
@@ -2948,7 +2957,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
         for (int k = 0; k < K; ++k) pre[k + 1] += pre[k];
     }
     __syncthreads();
-    const int32_t total = pre[K];
+    const int32_t total = __builtin_amdgcn_readfirstlane(pre[K]);
     // the range's entries, worker after worker, in batches of NB per thread:
     // one round of loads a batch, whichever workers they belong to, then the
     // additions worker by worker
@@ -2992,25 +3001,51 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
             lds_barrier();  // worker k's additions land before worker k+1's
         }
     }
-    int kb = 0;
+    // lane k: worker k's first entry and the one past its last
+    const int lane = t & (kWave - 1);
+    const int32_t from = lane < K ? pre[lane] : total, end = lane < K ? pre[lane + 1] : total;
     for (int32_t b0 = by_worker ? total : 0; b0 < total; b0 += NB * kGroup) {
         int32_t at[NB];  // worker << 16 | component of the range; -1: none
         float v[NB];
-        while (b0 >= pre[kb + 1]) ++kb;  // the worker of the batch's first entry
+        // the workers with entries in the batch
+        const uint64_t in_batch = ballot(end > from && end > b0 && from < b0 + NB * kGroup);
+        const int nu = total - b0 <= kGroup ? 1 : NB;  // rounds of loads
         {
             int32_t jj[NB];
-            int k = kb;
+            if (nu == 1) {
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {  // past the last entry: the last again, dropped below
-                const int32_t i = min(b0 + u * kGroup + t, total - 1);
-                while (i >= pre[k + 1]) ++k;
-                const int32_t pos = src[k] + (i - pre[k]);
-                at[u] = k;
-                jj[u] = idx[(size_t)k * idx_row + pos];
-                v[u] = val[(size_t)k * val_row + pos];
+                for (int u = 0; u < NB; ++u) at[u] = -1;
+                const int32_t i = b0 + t;
+                if (i < total) {
+                    int k = 0;
+                    for (uint64_t m = in_batch; m != 0ull; m &= m - 1ull) {
+                        const int q = (int)__ffsll((unsigned long long)m) - 1;
+                        if (i >= __builtin_amdgcn_readlane(from, q)) k = q;
+                    }
+                    const int32_t pos = src[k] + (i - pre[k]);
+                    at[0] = k;
+                    jj[0] = idx[(size_t)k * idx_row + pos];
+                    v[0] = val[(size_t)k * val_row + pos];
+                }
+            } else {  // past the last entry: the last again, dropped below
+#pragma unroll
+                for (int u = 0; u < NB; ++u) at[u] = 0;
+                for (uint64_t m = in_batch; m != 0ull; m &= m - 1ull) {
+                    const int q = (int)__ffsll((unsigned long long)m) - 1;
+                    const int32_t first = __builtin_amdgcn_readlane(from, q);
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) at[u] = min(b0 + u * kGroup + t, total - 1) >= first ? q : at[u];
+                }
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int32_t pos = src[at[u]] + (min(b0 + u * kGroup + t, total - 1) - pre[at[u]]);
+                    jj[u] = idx[(size_t)at[u] * idx_row + pos];
+                    v[u] = val[(size_t)at[u] * val_row + pos];
+                }
             }
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
+                if (u >= nu) break;
                 const int64_t rel = (int64_t)jj[u] - base;
                 const bool in = b0 + u * kGroup + t < total && rel >= 0 && rel < n;
                 if (in && f.zero_e) f.ez[at[u]][jj[u]] = v[u] - v[u];
@@ -3020,7 +3055,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
         if (early) {
 #pragma unroll
             for (int u = 0; u < NB; ++u)
-                if (at[u] >= 0) atomicOr(&hb[(at[u] & 0xffff) >> 5], 1u << (at[u] & 31));
+                if (u < nu && at[u] >= 0) atomicOr(&hb[(at[u] & 0xffff) >> 5], 1u << (at[u] & 31));
             lds_barrier();
 #pragma unroll
             for (int i = 0; i < V; ++i) {
@@ -3031,8 +3066,8 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
                 }
             }
         }
-        for (int k = kb; k < K && pre[k] < b0 + NB * kGroup; ++k) {
-            if (pre[k + 1] == pre[k]) continue;
+        for (uint64_t m = in_batch; m != 0ull; m &= m - 1ull) {
+            const int k = (int)__ffsll((unsigned long long)m) - 1;
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
                 if ((at[u] >> 16) == k) {
@@ -3086,7 +3121,6 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
             uint32_t mine = 0;
 #pragma unroll
             for (int i = 0; i < V; ++i) mine += (uint32_t)__popc(lm[i]);
-            const int lane = t & (kWave - 1);
             uint32_t incl = mine;
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {

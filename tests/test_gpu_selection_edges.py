@@ -1,7 +1,7 @@
 """The selection at the edges of its paths: segments at and around the size
 selected whole (4096), pairs at and around the sizes one workgroup takes (k =
-1024 and 14,000, 512 and 2048 chunks of 2048), ties, zeros and non-finite values in them, candidates
-crowded into a few chunks; and the server pass at and around its batch sizes.
+1024 and 14,000, 512 and 2048 chunks of 2048), ties, zeros and non-finite
+values in them, candidates crowded into a few chunks; and the server pass at and around its batch sizes.
 Everything against the oracle (or the sum in worker order), bit for bit."""
 import dataclasses
 
@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import synth
+from paper_1905_12948_amd.gmc import count
 from gpu_harness import Case, run_lockstep
 
 pytestmark = pytest.mark.gpu
@@ -125,17 +126,24 @@ def test_pair_stats_tell_the_paths_apart():
     assert mode.tolist() == [[2, 2, 1]] * K
 
 
-@pytest.mark.parametrize("K,per", [(1, 0), (1, 1024), (1, 1025), (3, 341), (3, 342), (4, 512), (4, 513), (16, 33),
-                                   (16, 65), (16, 600), (2, 4096), (64, 1), (64, 40)])
-def test_server_batches(K, per):
-    """Ranges of K * per entries: one batch, several, a round per worker."""
+# entries per worker in one range: one round of 256, one batch, several, a
+# round per worker, with the larger batch (1024 entries) and, where most ranges
+# are empty, the smaller one (512)
+DENSE = [(1, 0), (1, 1024), (1, 1025), (3, 341), (3, 342), (4, 512), (4, 513), (16, 33), (16, 65), (16, 600), (2, 4096),
+         (64, 1), (64, 40)]
+SPARSE = [(1, 1), (1, 256), (1, 257), (1, 513), (2, 128), (2, 129), (3, 170), (3, 171), (4, 200), (4, 300), (16, 16),
+          (16, 17), (16, 33), (16, 200), (64, 4), (64, 5), (64, 70)]
+
+
+@pytest.mark.parametrize("K,per,empty", [(K, n, 1) for K, n in DENSE] + [(K, n, 100) for K, n in SPARSE])
+def test_server_batches(K, per, empty):
     import torch
     from paper_1905_12948_amd.gmc import aggregate_static
-    d = 3 * 4096 + 5
+    d = (2 + empty) * 4096 + 5
     rng = np.random.default_rng(100 * K + per)
     n = per + 2
     idx = np.zeros((K, n), np.int32)
-    for k in range(K):  # the middle range gets `per` entries, the last components two
+    for k in range(K):  # the second range gets `per` entries, the last components two
         idx[k] = np.concatenate([4096 + np.sort(rng.choice(4096, per, replace=False)), [d - 2, d - 1]])
     val = rng.standard_normal((K, n)).astype(np.float32)
     want = np.zeros(d, np.float32)
@@ -146,3 +154,23 @@ def test_server_batches(K, per):
     aggregate_static(d, K, 0.1, torch.from_numpy(idx).to("cuda:0"), torch.from_numpy(val).to("cuda:0"),
                      torch.full((K,), n, dtype=torch.int64, device="cuda:0"), upd)
     assert np.array_equal(upd.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("calls", ["iteration", "two calls", "momentum on the server"])
+@pytest.mark.parametrize("K,per,empty", [(1, 1024, 1), (1, 1025, 1), (3, 341, 1), (3, 342, 1), (4, 600, 1), (16, 65, 1),
+                                         (2, 128, 100), (2, 129, 100), (2, 256, 100), (2, 257, 100), (4, 129, 100),
+                                         (4, 300, 100), (16, 16, 100), (16, 33, 100)])
+def test_server_batches_applied(K, per, empty, calls):
+    """The same with the update applied: every worker's whole message in one
+    range, where its gradients are a thousand times larger."""
+    d = (2 + empty) * 4096 + 5
+    how = {"iteration": dict(iteration=True, sparse_w=True), "two calls": dict(fused_apply=True, write_update=False),
+           "momentum on the server": dict(rule="server_momentum")}[calls]
+
+    def crowd(t, g):
+        g = g.copy()
+        g[:, 4096:8192] *= np.float32(1000)
+        return g
+    w = wl([d], per / d, comp="topk", K=K)
+    assert count(d, per / d) == per
+    run_lockstep(Case(w, steps=4, grad_hook=crowd, label="K %d per %d" % (K, per), **how), verbose=False)
