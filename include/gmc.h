@@ -131,8 +131,8 @@ gmc_status gmc_set_segments(gmc_ctx* ctx, int32_t n_seg, const int64_t* seg_off)
 /* GMC_RBGS only: block length B of the random blockwise compressor (RBGS,
  * Sections 4 and 5.2: whole blocks of consecutive components, drawn with a
  * seed the workers share).  1 <= B <= d; any B is accepted, a multiple of 4
- * is faster (a 16-byte access then never straddles blocks).  Before the first step only (GMC_ESTATE after).
- * Default 4096. */
+ * is faster (a 16-byte access then never straddles blocks).  Before the
+ * first step only (GMC_ESTATE after).  Default 4096. */
 gmc_status gmc_set_block(gmc_ctx* ctx, int32_t block);
 
 /* Stream all later calls enqueue on (a hipStream_t; NULL = null stream).

@@ -131,8 +131,8 @@ struct PairState {
     float growth;       // smoothed cand_used / tau_rank of the steps so far (0: not known)
     uint32_t unused;
     // exact top-s: the first pass puts the next step's threshold at the floor
-    // of the 11-bit bin tau_bin holding the key of rank margin*k/4; with
-    // tau_fine the second pass narrows it to the floor of the 22-bit bin
+    // of the 11-bit bin tau_bin holding the key of rank tau_rank (next_rank;
+    // below all candidates where they are fewer); with tau_fine the second pass narrows it to the floor of the 22-bit bin
     // holding that key, the tau_need-th of bin tau_bin from the top
     uint32_t tau_bin;
     uint32_t tau_need;

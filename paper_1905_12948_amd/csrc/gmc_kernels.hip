@@ -17,6 +17,10 @@
 //   topk_emit    ordered compaction of the kept components into the message,
 //                residual u - u at the kept components, and the server
 //                pass's row pointers
+//   topk_solo    all of that for a pair whose candidates fit one workgroup's
+//                LDS, in one launch; select_direct (in the copy's launch) for a
+//                segment of at most 4096 components, from u itself
+//   topk_seed    the first step's thresholds, from a sample of u
 //   rbgs_*       shared block draw and the fused pass that gathers whole blocks
 //   agg_*        the server sum over workers in worker order, the update and
 //                w_{t+1} = w_t + update
@@ -151,12 +155,6 @@ __device__ __forceinline__ float rule_u_rt(int rule, float e, float g, float wt,
     if (rule == kRuleServerMomentum) return rule_u<kRuleServerMomentum>(e, g, wt, wp, c, h);
     if (rule == kRuleLrInResidual) return rule_u<kRuleLrInResidual>(e, g, wt, wp, c, h);
     return rule_u<kRuleGmc>(e, g, wt, wp, c, h);
-}
-
-__device__ __forceinline__ float rule_u_diff_rt(int rule, float e, float g, float diff, float c, float h) {
-    if (rule == kRuleServerMomentum) return rule_u_diff<kRuleServerMomentum>(e, g, diff, c, h);
-    if (rule == kRuleLrInResidual) return rule_u_diff<kRuleLrInResidual>(e, g, diff, c, h);
-    return rule_u_diff<kRuleGmc>(e, g, diff, c, h);
 }
 
 // The output mix of SplitMix64 (Steele, Lea and Flood, OOPSLA 2014).
@@ -1195,7 +1193,7 @@ __device__ void finish_digit(PairState* ps, int p, uint32_t* h, uint32_t* gh, in
     }
     if (PASS == 2) {
         // the speculative threshold at the floor of the 22-bit bin holding
-        // the key of rank margin*k/4: the tau_need-th key of bin tau_bin
+        // the key of next_rank: the tau_need-th key of bin tau_bin
         if (tau_fine) {
             const uint32_t tb = tau_bin, tn = tau_need;
             int sb = bin;  // the threshold at T's own rank in T's bin: the bin found above

@@ -437,7 +437,7 @@ class Gmc:
         """(mode, cand) per (worker, segment) pair of the last step, as [K, n_seg]
         int arrays: mode 0 = resolved from the speculative candidates, 1 =
         full-data path, 2 = a segment of at most 4096 components, selected
-        whole; cand = candidates the worker pass collected."""""
+        whole; cand = candidates the worker pass collected."""
         import numpy as np
         np_ = ctypes.c_int32(0)
         self._call(self._lib.gmc_pair_stats(self._ctx, None, None, 0, ctypes.byref(np_)))

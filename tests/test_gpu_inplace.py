@@ -2,9 +2,8 @@
 writes w_{t+1} over w_t and keeps w_{t+1} - w_t as its change list, from
 which the next worker pass takes the momentum term of Algorithm 1 with
 w_prev = NULL.  Every output against the oracle, step by step: global,
-per-tensor (partial chunks, element-wise path) and sampled-threshold top-s,
-the learning-rate-in-residual rule, misaligned rows (the element-wise
-kernel), non-finite parameters, ranges whose every component changes; and
+per-tensor (partial chunks) and sampled-threshold top-s, the
+learning-rate-in-residual rule, misaligned rows, non-finite parameters, ranges whose every component changes; and
 the call-order errors of the mode."""
 import numpy as np
 import pytest
@@ -43,8 +42,7 @@ def test_inplace_matches_the_oracle(name, shrink, K, extra, mode):
 
 
 def test_inplace_misaligned_rows_and_ragged_segments():
-    # rows one float off 16-byte alignment (the element-wise kernel, one
-    # wavefront per chunk) and segments that start mid-chunk
+    # rows one float off 16-byte alignment and segments that start mid-chunk
     wl = synth.Workload("odd", [5000, 3, 77777, 2048 * 3 + 1], K=3, ratio=0.01, beta=0.9, eta=0.1,
                         steps=4, compressor="topk_seg", dist="normal")
     st = run_lockstep(Case(wl, steps=4, row_pad=1, inplace="iteration", sparse_w=True, options=FULL_LIST,

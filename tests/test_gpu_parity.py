@@ -152,8 +152,8 @@ def test_rbgs_more_blocks_than_the_lds_bitmap():
 def test_sparse_messages_with_one_dense_range():
     # 200 one-component tensors (k = 1 each) fill the first range, ten large
     # tensors follow: on average 15 message entries per range, so the server
-    # pass stages few entries per range, while the first range holds more
-    # than 600 and is summed worker after worker from the messages
+    # pass takes its smaller batch, while the first range holds more than 600
+    # and needs several
     wl = synth.Workload("dense-first", [1] * 200 + [100_000] * 10, K=3, ratio=0.001, beta=0.9, eta=0.1, steps=3,
                         compressor="topk_seg", dist="normal")
     run_lockstep(Case(wl, steps=3, label="one dense range"))
@@ -386,10 +386,9 @@ def test_iteration_with_non_finite_parameters():
 def test_server_pass_ranges_beyond_the_wave_stage(iteration):
     """Sparse messages on average, but clustered: the largest gradients all
     sit in the first 12288 components, so the first three 4096-component
-    ranges hold every worker's whole message (thousands of entries, more
-    than the one-wavefront server pass stages) while the other ranges hold
-    none.  Those ranges take the block kernel after the one-wavefront pass;
-    every output against the oracle."""
+    ranges hold every worker's whole message (thousands of entries, a round
+    per worker) while the other ranges hold none; every output against the
+    oracle."""
     wl = synth.Workload("clustered", [1 << 22], K=4, ratio=0.002, beta=0.9, eta=0.1, steps=4,
                         compressor="topk", dist="normal")
 
