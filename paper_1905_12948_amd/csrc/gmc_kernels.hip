@@ -1033,7 +1033,8 @@ hipError_t launch_topk_seed(const StepArgs& a, const TopkGeometry& g, const Topk
 // n/k steps a component is sent as often as it reaches the threshold), and
 // then rank k leaves too few candidates every other step, which costs a
 // full-data selection (d = 2^20, K = 4, 1%: 188 us per step after 2000 steps
-// against 69 us; d = 11.2M, K = 8, 1%: 360 against 282 us).
+// against 69 us; a ResNet-18's tensors, K = 8, 1%: 319 against 290 us; in
+// their first tens of steps both ranks are k and so are the times).
 // So the rank aims at k + k/32 + 4 sqrt(k) candidates (the fluctuation of a
 // count, and 3% for steps that differ), but is never below margin * k / 4.
 // growth: smoothed over the steps, quick to fall and slow to rise, 0.8 until
