@@ -2856,9 +2856,12 @@ hipError_t launch_agg_rowptr(int32_t K, int32_t d, const int32_t* idx, int64_t i
 // are found from their first positions, one per lane, read by scalar: with
 // every thread's NB loads whatever the range held, and a chain of LDS reads
 // for each worker, messages spread evenly (d = 25.6M, K = 16, 0.1%) took 39.0
-// us for the dense update and 56.7 in an iteration, 29.2 and 50.8 so.  (Eight
-// workers' 0.1% of a decoder's tensors are the exception, 190.8 us with those
-// and 198.8 so, 204.6 with a round per worker.)
+// us for the dense update and 56.7 in an iteration, 29.2 and 50.8 so.  The
+// apply of the smaller batch keeps those loads and that chain (kChain): it
+// waits for memory, whose lines of w and e it touches one component each, and
+// is the faster for it (0.1% of a decoder's tensors, K = 8, 191.8 us so, 200.4
+// with the scalar search; d = 101M in place, K = 1, 1% 121 and 135; d = 60M,
+// K = 4, 0.1% 74.0 and 78.6; but d = 11.2M, K = 8, 0.1% 19.9 and 19.0).
 // Sent components are kept as a bitmap (hb), so a
 // workgroup needs 19 KB of LDS (eight fit on a CU, and NB = 4 keeps the
 // registers at eight wavefronts per SIMD): the kernel is bound by its chain of
@@ -2870,6 +2873,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
                                                           int64_t idx_row, const float* val, int64_t val_row,
                                                           const int32_t* rowptr, int32_t n_ranges, FinishArgs f) {
     constexpr int R = kAggTopkRange, NW = R / 32, V = R / (kGroup * 4);
+    constexpr bool kChain = kApply && !kPrev && NB == kAggTopkBatchSmall;
     static_assert(V * kGroup * 4 == R && NW <= kGroup, "whole float4 per thread, one word per thread");
     __shared__ float acc[R];
     __shared__ uint32_t hb[NW];  // components some worker sent
@@ -3003,15 +3007,29 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
     // lane k: worker k's first entry and the one past its last
     const int lane = t & (kWave - 1);
     const int32_t from = lane < K ? pre[lane] : total, end = lane < K ? pre[lane + 1] : total;
+    int kb = 0;
     for (int32_t b0 = by_worker ? total : 0; b0 < total; b0 += NB * kGroup) {
         int32_t at[NB];  // worker << 16 | component of the range; -1: none
         float v[NB];
         // the workers with entries in the batch
-        const uint64_t in_batch = ballot(end > from && end > b0 && from < b0 + NB * kGroup);
-        const int nu = total - b0 <= kGroup ? 1 : NB;  // rounds of loads
+        const uint64_t in_batch = kChain ? 0ull : ballot(end > from && end > b0 && from < b0 + NB * kGroup);
+        const int nu = !kChain && total - b0 <= kGroup ? 1 : NB;  // rounds of loads
+        if (kChain)
+            while (b0 >= pre[kb + 1]) ++kb;  // the worker of the batch's first entry
         {
             int32_t jj[NB];
-            if (nu == 1) {
+            if (kChain) {  // past the last entry: the last again, dropped below
+                int k = kb;
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const int32_t i = min(b0 + u * kGroup + t, total - 1);
+                    while (i >= pre[k + 1]) ++k;
+                    const int32_t pos = src[k] + (i - pre[k]);
+                    at[u] = k;
+                    jj[u] = idx[(size_t)k * idx_row + pos];
+                    v[u] = val[(size_t)k * val_row + pos];
+                }
+            } else if (nu == 1) {
 #pragma unroll
                 for (int u = 0; u < NB; ++u) at[u] = -1;
                 const int32_t i = b0 + t;
@@ -3026,7 +3044,7 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
                     jj[0] = idx[(size_t)k * idx_row + pos];
                     v[0] = val[(size_t)k * val_row + pos];
                 }
-            } else {  // past the last entry: the last again, dropped below
+            } else {
 #pragma unroll
                 for (int u = 0; u < NB; ++u) at[u] = 0;
                 for (uint64_t m = in_batch; m != 0ull; m &= m - 1ull) {
@@ -3065,8 +3083,15 @@ __global__ __launch_bounds__(kGroup) void agg_topk_kernel(int32_t K, int32_t d, 
                 }
             }
         }
-        for (uint64_t m = in_batch; m != 0ull; m &= m - 1ull) {
-            const int k = (int)__ffsll((unsigned long long)m) - 1;
+        // worker by worker: with kChain k counts up, else it takes in_batch's bits
+        uint64_t m = in_batch;
+        for (int k = kb; kChain ? (k < K && pre[k] < b0 + NB * kGroup) : m != 0ull; ++k) {
+            if (kChain) {
+                if (pre[k + 1] == pre[k]) continue;
+            } else {
+                k = (int)__ffsll((unsigned long long)m) - 1;
+                m &= m - 1ull;
+            }
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
                 if ((at[u] >> 16) == k) {
