@@ -1220,6 +1220,7 @@ __device__ uint32_t pair_candidates(const StepArgs& a, const TopkGeometry& g, co
     return all;
 }
 
+// marks: topk_solo_kernel was launched, and has marked the pairs it took.
 // The third pass of exact top-s also takes the count of the kept components
 // per slice: each workgroup stores its slice's count above T's 22-bit bin and
 // the suffix sums of its 512-bin histogram of that bin (sl_hist, kSlHist
@@ -1227,7 +1228,7 @@ __device__ uint32_t pair_candidates(const StepArgs& a, const TopkGeometry& g, co
 // slice's counts above and at T and lays out the message.
 template <int PASS>
 __device__ void hist_pass(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full,
-                          int margin, int64_t* msg_len, int64_t msg_total, int blk) {
+                          int margin, int64_t* msg_len, int64_t msg_total, int blk, bool marks) {
     constexpr int nbins = PASS == 3 ? 512 : kBins;
     __shared__ uint32_t h[kBins];
     __shared__ uint32_t h2[PASS == 2 ? kBins : 1];
@@ -1238,11 +1239,7 @@ __device__ void hist_pass(const StepArgs& a, const TopkGeometry& g, const TopkSc
 
     const SliceId id = slice_id(g, blk);
     PairState* ps = &s.pair[id.p];
-    // topk_solo_kernel wrote the message.  The first pass needs no look at the
-    // mark: such a pair's candidates number between k and the capacity, so it
-    // leaves below (and the look costs topk_copy_pass1_kernel<false> a register
-    // too many)
-    if (PASS != 1 && g.n_solo != 0 && ps->mode == kModeDone) return;
+    if (marks && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
     // sampled-threshold top-s: the passes select over the sample, rank samp_r
     const bool approx = g.approx != 0;
     const int kp = approx ? g.samp_r : g.pair_k[id.p];
@@ -1418,7 +1415,7 @@ template <int PASS>
 __global__ __launch_bounds__(kGroup) void topk_hist_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
                                                            int force_full, int margin, int64_t* msg_len,
                                                            int64_t msg_total) {
-    hist_pass<PASS>(a, g, s, force_full, margin, msg_len, msg_total, blockIdx.x);
+    hist_pass<PASS>(a, g, s, force_full, margin, msg_len, msg_total, blockIdx.x, g.n_solo != 0);
 }
 
 hipError_t launch_topk_hist(int pass, const StepArgs& a, const TopkGeometry& g, const TopkScratch& s,
@@ -1453,7 +1450,7 @@ hipError_t launch_topk_hist(int pass, const StepArgs& a, const TopkGeometry& g, 
 constexpr int kMaxCopyTiles = 256;  // tiles of one workgroup (at most about cap_mult / 8 + 2)
 
 __device__ void compact_copy(const StepArgs& a, const TopkGeometry& g, const TopkScratch& s, int force_full, int margin,
-                             int blk) {
+                             int blk, bool marks) {
     __shared__ uint32_t pre[kCompactChunks];
     __shared__ uint32_t h[kBins];
     __shared__ uint32_t sh_wsum[kWavesPerGroup];
@@ -1473,7 +1470,7 @@ __device__ void compact_copy(const StepArgs& a, const TopkGeometry& g, const Top
     const int seg = tm.x;
     const int p = k * g.n_seg + seg;
     PairState* ps = &s.pair[p];
-    if (g.n_solo != 0 && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
+    if (marks && ps->mode == kModeDone) return;  // topk_solo_kernel wrote the message
     const uint32_t i0 = (uint32_t)tm.y;
     const uint32_t stride = (uint32_t)g.seg_tile_stride[seg];
     // the pair's groups: totals, list bases and tiles, in blocks of kGroup
@@ -1685,10 +1682,13 @@ __device__ void select_direct(const StepArgs& a, const TopkGeometry& g, const To
 // top-s); both decide which pairs those are from the groups' totals.  The last
 // K * n_direct select the direct segments, whole (kDirect: there are any).  The
 // copy keeps its workgroups resident, seven wavefronts per SIMD by LDS, with 72
-// registers (kDirect false); the direct segments' code brings it to 76, six
-// wavefronts.  With six the copy of a context without direct segments took 21.8
-// us for 21.5 (d = 25.6M, K = 16, 0.1%), 13.7 for 13.6 (K = 4, 0.01%).
-template <bool kDirect>
+// registers; the direct segments' code brings it to 76, six wavefronts, as did
+// (73) a run-time test of whether topk_solo_kernel was launched (kSolo).  With six
+// the copy of a context with neither took 21.8 us for 21.5 (d = 25.6M, K = 16,
+// 0.1%), 13.7 for 13.6 (K = 4, 0.01%); without the look at the marks the
+// workgroups of pairs that have their message sum the candidates first (tiny: a
+// step 55.1 us for 53.5).
+template <bool kDirect, bool kSolo>
 __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, TopkGeometry g, TopkScratch s,
                                                                  int force_full, int margin, int32_t* idx, float* val,
                                                                  int64_t row_len, int64_t* msg_len,
@@ -1696,9 +1696,9 @@ __global__ __launch_bounds__(kGroup) void topk_copy_pass1_kernel(StepArgs a, Top
     const int n_copy = g.K * g.tiles_per_worker, n_hist = n_copy + g.K * g.n_slices;
     const int b = blockIdx.x;
     if (b < n_copy)
-        compact_copy(a, g, s, force_full, margin, b);
+        compact_copy(a, g, s, force_full, margin, b, kSolo);
     else if (!kDirect || b < n_hist)
-        hist_pass<1>(a, g, s, force_full, margin, nullptr, 0, b - n_copy);
+        hist_pass<1>(a, g, s, force_full, margin, nullptr, 0, b - n_copy, kSolo);
     else if (kDirect)
         select_direct(a, g, s, (b - n_hist) / g.n_direct, g.direct_seg[(b - n_hist) % g.n_direct], idx, val, row_len,
                       msg_len, msg_total);
@@ -1712,8 +1712,10 @@ hipError_t launch_topk_compact(const StepArgs& a, const TopkGeometry& g, const T
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kGroup), 0, st, a, g, s, force_full, margin, idx, val,
                            row_len, msg_len, msg_total);
     };
-    if (g.n_direct) launch(topk_copy_pass1_kernel<true>);
-    else launch(topk_copy_pass1_kernel<false>);
+    if (g.n_direct && g.n_solo) launch(topk_copy_pass1_kernel<true, true>);
+    else if (g.n_direct) launch(topk_copy_pass1_kernel<true, false>);
+    else if (g.n_solo) launch(topk_copy_pass1_kernel<false, true>);
+    else launch(topk_copy_pass1_kernel<false, false>);
     return hipGetLastError();
 }
 

@@ -52,6 +52,6 @@ def test_dynamic_lds_of_the_one_workgroup_selection_is_16_byte_aligned(kernels):
 
 def test_the_copy_keeps_seven_wavefronts_per_simd(kernels):
     # 512 registers per lane and SIMD, allocated by eights; no scratch
-    for k in named(kernels, "topk_copy_pass1_kernelILb0E"):
+    for k in named(kernels, "topk_copy_pass1_kernelILb0ELb0E"):
         assert k[".vgpr_count"] <= 72 and k[".private_segment_fixed_size"] == 0, k[".vgpr_count"]
         assert 7 * k[".group_segment_fixed_size"] <= 160 * 1024
