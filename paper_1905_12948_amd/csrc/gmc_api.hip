@@ -272,8 +272,9 @@ int64_t pair_launch(const gmc_ctx* ctx, int64_t n, int64_t k) {
 // takes only some pairs the four launches of the others follow in full, and
 // where it needs two launches they cost what it saves (d = 2.8M per tensor, K =
 // 4: 92 us a step with one launch of each size, 88 without, 79 with one).
-//   k: the usual candidates, 1.05-1.17 k once the residual has built up, fit in
-//   LDS up to k = 14,000.
+//   k: the usual candidates, 1.05-1.12 k once the residual has built up, fit in
+//   LDS up to k = 14,600 (K = 4 or 8, 1%: 61 us a step for 70 at k = 14,500, 77
+//   for 84 at 14,800, but 84 for 71 at 15,000, where every other step's do not).
 //   Length: the gather walks the chunks in one workgroup whatever it finds in
 //   them, 16 us less than the four launches at 300 chunks, 4 us at 1950, and 6
 //   us more at 2930 with 1024 threads; 9 us less at 390, 1 us at 780 and 14 us

@@ -88,7 +88,7 @@ constexpr int kSoloBins = 4096;
 constexpr int kSoloCands = 16 * 1024;
 constexpr int kSoloSmallCands = 4096;
 constexpr int kSoloSmallK = 1024;
-constexpr int kSoloMaxK = 14000;           // the 1.05-1.17 k candidates of a steady state fit
+constexpr int kSoloMaxK = 14600;           // the usual 1.05-1.12 k candidates of a steady state fit
 constexpr int kDirectMax = 4096;
 constexpr int kModeDone = 4;
 constexpr int kModePending = -1;

@@ -1,6 +1,6 @@
 """The selection at the edges of its paths: segments at and around the size
 selected whole (4096), pairs at and around the sizes one workgroup takes (k =
-1024 and 14,000, 512 and 2048 chunks of 2048), ties, zeros and non-finite
+1024 and 14,600, 512 and 2048 chunks of 2048), ties, zeros and non-finite
 values in them, candidates crowded into a few chunks; and the server pass at and around its batch sizes.
 Everything against the oracle (or the sum in worker order), bit for bit."""
 import dataclasses
@@ -43,7 +43,7 @@ HOOKS = {
     ([102_400], 0.01, True),                            # k = 1024: the smaller workgroup's largest
     ([102_401], 0.01, True),                            # k = 1025
     ([46_666, 6000], 0.3, True),                        # k = 14,000 beside a small pair, in one launch
-    ([46_667, 6000], 0.3, False),                       # k = 14,001: the multi-workgroup passes
+    ([48_667, 6000], 0.3, False),                       # k = 14,601: the multi-workgroup passes
     ([50_000, 6000], 0.3, False),
 ])
 def test_selection_paths(sizes, ratio, solo, hook):
